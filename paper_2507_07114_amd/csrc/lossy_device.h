@@ -35,6 +35,8 @@ constexpr int kBatchGrad = 4;
 constexpr int kBatchDrift = 2;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds, each
@@ -83,10 +85,12 @@ __device__ __forceinline__ bool bernoulli_arrived(uint64_t k, uint64_t i, uint64
 struct F32 {
     typedef float T;
     static constexpr int kPacketThreads = 128;
+    static constexpr bool kSplit = true;  // see Chunk
 };
 struct BF16 {
     typedef uint16_t T;
     static constexpr int kPacketThreads = 256;
+    static constexpr bool kSplit = false;
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
@@ -97,16 +101,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// Memory access of a thread's 8 consecutive elements.  Kernels decide per
-// tile (wave-uniformly) which of two forms every access of the tile takes:
-//   W = true   every thread of the tile owns 0 or 8 elements and the tile
-//              starts on a 16-byte boundary: one 16-byte access per 8 bf16
-//              (two per 8 fp32), predicated on nv == 8.  Loads land in raw
-//              registers and are unpacked only when used, so a batch of row
-//              loads is in flight together.
-//   W = false  element by element (a shard end that is not a multiple of 8,
-//              or packets whose length is not a multiple of 8 elements).
-// Raw storage of 8 consecutive elements.
+// Raw storage of a thread's 8 elements.
 template <class E>
 struct Raw8;
 template <>
@@ -117,38 +112,6 @@ template <>
 struct Raw8<BF16> {
     u32x4 a;
 };
-
-template <bool W>
-__device__ __forceinline__ void load_raw(const float* p, int nv, Raw8<F32>& r) {
-    r.a = u32x4{0, 0, 0, 0};
-    r.b = u32x4{0, 0, 0, 0};
-    if (W) {
-        if (nv == 8) {
-            r.a = *reinterpret_cast<const u32x4*>(p);
-            r.b = *reinterpret_cast<const u32x4*>(p + 4);
-        }
-    } else {
-        uint32_t w[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = j < nv ? __float_as_uint(p[j]) : 0u;
-        r.a = u32x4{w[0], w[1], w[2], w[3]};
-        r.b = u32x4{w[4], w[5], w[6], w[7]};
-    }
-}
-
-template <bool W>
-__device__ __forceinline__ void load_raw(const uint16_t* p, int nv, Raw8<BF16>& r) {
-    r.a = u32x4{0, 0, 0, 0};
-    if (W) {
-        if (nv == 8) r.a = *reinterpret_cast<const u32x4*>(p);
-    } else {
-        uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j < nv) w[j >> 1] |= (uint32_t)p[j] << (16 * (j & 1));
-        r.a = u32x4{w[0], w[1], w[2], w[3]};
-    }
-}
 
 __device__ __forceinline__ void unpack(const Raw8<F32>& r, float (&x)[8]) {
     x[0] = __uint_as_float(r.a.x); x[1] = __uint_as_float(r.a.y);
@@ -164,130 +127,19 @@ __device__ __forceinline__ void unpack(const Raw8<BF16>& r, float (&x)[8]) {
     x[6] = bf16_to_f32(r.a.w & 0xFFFFu); x[7] = bf16_to_f32(r.a.w >> 16);
 }
 
-// 8 consecutive elements as floats (0 past nv).
-template <class E, bool W>
-__device__ __forceinline__ void load8(const typename E::T* p, int nv, float (&x)[8]) {
-    Raw8<E> r;
-    load_raw<W>(p, nv, r);
-    unpack(r, x);
+// Rounded storage form of 8 values (what a row of type E holds).
+__device__ __forceinline__ void pack(const float (&x)[8], Raw8<F32>& r) {
+    r.a = u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]),
+                __float_as_uint(x[3])};
+    r.b = u32x4{__float_as_uint(x[4]), __float_as_uint(x[5]), __float_as_uint(x[6]),
+                __float_as_uint(x[7])};
 }
 
-// Rounded storage form of 8 values (what a replica row holds).
-template <class E>
-struct Packed8;
-
-template <>
-struct Packed8<F32> {
-    Raw8<F32> r;
-    __device__ __forceinline__ void pack(const float (&x)[8]) {
-        r.a = u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]),
-                    __float_as_uint(x[3])};
-        r.b = u32x4{__float_as_uint(x[4]), __float_as_uint(x[5]), __float_as_uint(x[6]),
-                    __float_as_uint(x[7])};
-    }
-    __device__ __forceinline__ float value(int j) const {
-        const u32x4& h = j < 4 ? r.a : r.b;
-        const int q = j & 3;
-        return __uint_as_float(q == 0 ? h.x : q == 1 ? h.y : q == 2 ? h.z : h.w);
-    }
-    template <bool W>
-    __device__ __forceinline__ void store(float* p, int nv) const {
-        if (W) {
-            if (nv == 8) {
-                __builtin_nontemporal_store(r.a, reinterpret_cast<u32x4*>(p));
-                __builtin_nontemporal_store(r.b, reinterpret_cast<u32x4*>(p + 4));
-            }
-        } else {
-            for (int j = 0; j < nv; ++j) p[j] = value(j);
-        }
-    }
-};
-
-template <>
-struct Packed8<BF16> {
-    Raw8<BF16> r;
-    __device__ __forceinline__ void pack(const float (&x)[8]) {
-        r.a = u32x4{f32_to_bf16(x[0]) | (f32_to_bf16(x[1]) << 16),
-                    f32_to_bf16(x[2]) | (f32_to_bf16(x[3]) << 16),
-                    f32_to_bf16(x[4]) | (f32_to_bf16(x[5]) << 16),
-                    f32_to_bf16(x[6]) | (f32_to_bf16(x[7]) << 16)};
-    }
-    __device__ __forceinline__ float value(int j) const {
-        const int q = j >> 1;
-        const uint32_t w = q == 0 ? r.a.x : q == 1 ? r.a.y : q == 2 ? r.a.z : r.a.w;
-        return bf16_to_f32((j & 1) ? (w >> 16) : (w & 0xFFFFu));
-    }
-    template <bool W>
-    __device__ __forceinline__ void store(uint16_t* p, int nv) const {
-        if (W) {
-            if (nv == 8) __builtin_nontemporal_store(r.a, reinterpret_cast<u32x4*>(p));
-        } else {
-            for (int j = 0; j < nv; ++j) p[j] = (uint16_t)f32_to_bf16(value(j));
-        }
-    }
-};
-
-template <bool W>
-__device__ __forceinline__ void store_f32x8(float* p, int nv, const float (&x)[8]) {
-    if (W) {
-        if (nv == 8) {
-            *reinterpret_cast<u32x4*>(p) = u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]),
-                                                 __float_as_uint(x[2]), __float_as_uint(x[3])};
-            *reinterpret_cast<u32x4*>(p + 4) = u32x4{__float_as_uint(x[4]), __float_as_uint(x[5]),
-                                                     __float_as_uint(x[6]), __float_as_uint(x[7])};
-        }
-    } else {
-        for (int j = 0; j < nv; ++j) p[j] = x[j];
-    }
-}
-
-// Store raw storage back bit for bit (16-byte non-temporal stores when W).
-template <bool W>
-__device__ __forceinline__ void store_raw(float* p, int nv, const Raw8<F32>& r) {
-    if (W) {
-        if (nv == 8) {
-            __builtin_nontemporal_store(r.a, reinterpret_cast<u32x4*>(p));
-            __builtin_nontemporal_store(r.b, reinterpret_cast<u32x4*>(p + 4));
-        }
-    } else {
-        const uint32_t w[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
-        for (int j = 0; j < nv; ++j) p[j] = __uint_as_float(w[j]);
-    }
-}
-
-template <bool W>
-__device__ __forceinline__ void store_raw(uint16_t* p, int nv, const Raw8<BF16>& r) {
-    if (W) {
-        if (nv == 8) __builtin_nontemporal_store(r.a, reinterpret_cast<u32x4*>(p));
-    } else {
-        const uint32_t w[4] = {r.a.x, r.a.y, r.a.z, r.a.w};
-        for (int j = 0; j < nv; ++j) p[j] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Row loads through a buffer resource (CDNA buffer instructions).  The
-// resource of a row's chunk has the chunk's valid bytes as its size, so a
-// lane past the data reads zeros without touching memory, and a resource of
-// size 0 gives a load that moves nothing.  Streaming loops issue such a load
-// unconditionally on every lane, so each iteration has the same number of
-// loads in flight and the compiler waits for one row at a time instead of
-// draining every load.
-// ---------------------------------------------------------------------------
-constexpr int kBufferWord3 = 0x00020000;  // gfx9-family word 3: 32-bit data format
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes,
-                                             kBufferWord3);
-}
-
-__device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t r, int lane_bytes, Raw8<BF16>& x) {
-    x.a = __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes, 0, 0);
-}
-
-__device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t r, int lane_bytes, Raw8<F32>& x) {
-    x.a = __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes, 0, 0);
-    x.b = __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes + 16, 0, 0);
+__device__ __forceinline__ void pack(const float (&x)[8], Raw8<BF16>& r) {
+    r.a = u32x4{f32_to_bf16(x[0]) | (f32_to_bf16(x[1]) << 16),
+                f32_to_bf16(x[2]) | (f32_to_bf16(x[3]) << 16),
+                f32_to_bf16(x[4]) | (f32_to_bf16(x[5]) << 16),
+                f32_to_bf16(x[6]) | (f32_to_bf16(x[7]) << 16)};
 }
 
 // Wave-uniform copy of a 64-bit value held identically by all active lanes.
@@ -392,26 +244,42 @@ __device__ __forceinline__ int popcount_words(const uint64_t* words, int nw) {
 
 // ---------------------------------------------------------------------------
 // Tiles of the per-packet kernels: a workgroup of NT threads owns a chunk of
-// NT * 8 elements of one packet, thread t elements e0 .. e0 + nv - 1.
+// NT * 8 elements of one packet, thread t two groups of four consecutive
+// elements of it.
+//   SPLIT = false  (geometry of bf16 rows) the groups are adjacent: a row
+//                  access is one 16-byte access per thread, 1 KiB of
+//                  contiguous memory per wavefront.
+//   SPLIT = true   (geometry of fp32 rows) the second group lies NT * 4
+//                  elements after the first, so that each of a row's two
+//                  16-byte accesses is contiguous over the wavefront too.
+//                  With adjacent groups every access touches half of each
+//                  128-byte line it spans; non-temporal stores of that form
+//                  reach 2.1 TB/s over 16 or 64 long rows where contiguous
+//                  ones reach 5.6, and a row read and written 4.4 against 5.3.
 // ---------------------------------------------------------------------------
+template <bool SPLIT>
 struct Chunk {
+    static constexpr bool split = SPLIT;
     int64_t k;    // packet
     int c;        // chunk within the packet
     int64_t c0;   // first element of the chunk
     int cv;       // valid elements of the chunk (0 .. NT * 8)
-    int64_t e0;   // first element of this thread
-    int lane;     // e0 - c0
-    int nv;       // valid elements of this thread (0..8)
-    bool whole;   // wave-uniform: every thread owns 0 or 8 elements, 16-byte aligned
+    int lane;     // first element of this thread's first group, from c0
+    int hi;       // of its second group
+    int nv;       // valid elements of this thread (0..8), a prefix of its 8
+    bool whole;   // wave-uniform: every group is full or empty, 16-byte aligned
+    __device__ __forceinline__ int64_t at(int j) const {
+        return c0 + (j < 4 ? lane + j : hi + j - 4);
+    }
 };
 
 // Chunk of tile b (tile = packet * cpp + chunk within the packet).  A chunk
 // is whole when it starts on a multiple of 8 elements and its valid part
 // ends on one or fills it: then every access of the tile can be a 16-byte
 // vector (row starts are 16-byte aligned).
-template <int NT>
-__device__ __forceinline__ Chunk chunk_at(int64_t b, int64_t d, int64_t L, int cpp) {
-    Chunk ch;
+template <int NT, bool SPLIT>
+__device__ __forceinline__ Chunk<SPLIT> chunk_at(int64_t b, int64_t d, int64_t L, int cpp) {
+    Chunk<SPLIT> ch;
     ch.k = b / cpp;
     ch.c = (int)(b - ch.k * cpp);
     const int64_t pk0 = ch.k * L;
@@ -419,69 +287,156 @@ __device__ __forceinline__ Chunk chunk_at(int64_t b, int64_t d, int64_t L, int c
     ch.c0 = pk0 + (int64_t)ch.c * (NT * kElems);
     const int64_t cv = pend - ch.c0;
     ch.cv = cv <= 0 ? 0 : (cv >= NT * kElems ? NT * kElems : (int)cv);
-    ch.lane = (int)threadIdx.x * kElems;
-    ch.e0 = ch.c0 + ch.lane;
-    const int64_t rem = pend - ch.e0;
-    ch.nv = rem <= 0 ? 0 : (rem >= 8 ? 8 : (int)rem);
+    ch.lane = (int)threadIdx.x * (SPLIT ? 4 : 8);
+    ch.hi = ch.lane + (SPLIT ? NT * 4 : 4);
+    const int lo_v = ch.cv - ch.lane, hi_v = ch.cv - ch.hi;
+    ch.nv = (lo_v <= 0 ? 0 : lo_v >= 4 ? 4 : lo_v) + (hi_v <= 0 ? 0 : hi_v >= 4 ? 4 : hi_v);
     ch.whole = (ch.c0 % 8 == 0) && ((pend - ch.c0) % 8 == 0 || pend >= ch.c0 + NT * kElems);
     return ch;
 }
 
+// ---------------------------------------------------------------------------
 // Accesses of a thread's 8 elements of the chunk of a contiguous array or
-// row (`base` points at its element 0).  Whole tiles (W) go through a buffer
-// resource holding the chunk's valid bytes: its base is the same for every
-// lane, each lane adds a 32-bit offset, and lanes past the data read zeros
-// and write nothing.  Other tiles take the element-by-element form.
-template <class T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const T* base, const Chunk& ch) {
+// row (`base` points at its element 0), in one of two forms decided per tile:
+//   W = true   (whole tiles) through a buffer resource (CDNA buffer
+//              instructions) holding the chunk's valid bytes: its base is the
+//              same for every lane, each lane adds a 32-bit offset, and lanes
+//              past the data read zeros and write nothing, without a branch.
+//   W = false  element by element (a shard end that is not a multiple of 8,
+//              or packets whose length is not a multiple of 8 elements).
+// Loads land in raw registers and are unpacked only when used, so several row
+// loads can be in flight together.
+// ---------------------------------------------------------------------------
+constexpr int kBufferWord3 = 0x00020000;  // gfx9-family word 3: 32-bit data format
+// Cache-policy bit of a non-temporal buffer access (gfx940-family `nt`).
+constexpr int kBufferNonTemporal = 2;
+
+// Cache policy of rows of type E.  A row element is read or written once per
+// step, so rows stream past the caches: 64 long rows read at 6.8 TB/s
+// non-temporally, 6.0 without.  fp32 rows in the geometry of bf16 ones touch
+// half lines and keep the plain policy (see Chunk).
+template <class E, bool SPLIT>
+constexpr int row_policy() {
+    return sizeof(typename E::T) == 2 || SPLIT ? kBufferNonTemporal : 0;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes,
+                                             kBufferWord3);
+}
+
+template <class T, bool SPLIT>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const T* base,
+                                                             const Chunk<SPLIT>& ch) {
     return row_rsrc(base + ch.c0, ch.cv * (int)sizeof(T));
 }
 
-template <bool W>
-__device__ __forceinline__ void load_chunk(const float* base, const Chunk& ch, Raw8<F32>& r) {
-    if (W) load_buf(chunk_rsrc(base, ch), ch.lane * 4, r);
-    else load_raw<false>(base + ch.e0, ch.nv, r);
+template <int POLICY, bool SPLIT>
+__device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t r, const Chunk<SPLIT>& ch,
+                                         Raw8<F32>& x) {
+    x.a = __builtin_amdgcn_raw_buffer_load_b128(r, ch.lane * 4, 0, POLICY);
+    x.b = __builtin_amdgcn_raw_buffer_load_b128(r, ch.hi * 4, 0, POLICY);
 }
 
-// Plain (temporal) stores: master and moments are read again next step.
-template <bool W>
-__device__ __forceinline__ void store_chunk(float* base, const Chunk& ch, const float (&x)[8]) {
-    if (W) {
-        const __amdgpu_buffer_rsrc_t r = chunk_rsrc(base, ch);
-        const u32x4 a = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]),
-                         __float_as_uint(x[3])};
-        const u32x4 b = {__float_as_uint(x[4]), __float_as_uint(x[5]), __float_as_uint(x[6]),
-                         __float_as_uint(x[7])};
-        __builtin_amdgcn_raw_buffer_store_b128(a, r, ch.lane * 4, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(b, r, ch.lane * 4 + 16, 0, 0);
+template <int POLICY, bool SPLIT>
+__device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t r, const Chunk<SPLIT>& ch,
+                                         Raw8<BF16>& x) {
+    if (SPLIT) {
+        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(r, ch.lane * 2, 0, POLICY);
+        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(r, ch.hi * 2, 0, POLICY);
+        x.a = u32x4{lo.x, lo.y, hi.x, hi.y};
     } else {
-        store_f32x8<false>(base + ch.e0, ch.nv, x);
+        x.a = __builtin_amdgcn_raw_buffer_load_b128(r, ch.lane * 2, 0, POLICY);
     }
 }
 
-// Cache-policy bit of a non-temporal buffer store (gfx940-family `nt`).
-constexpr int kBufferNonTemporal = 2;
+template <int POLICY, bool SPLIT>
+__device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, const Chunk<SPLIT>& ch,
+                                          const Raw8<F32>& x) {
+    __builtin_amdgcn_raw_buffer_store_b128(x.a, r, ch.lane * 4, 0, POLICY);
+    __builtin_amdgcn_raw_buffer_store_b128(x.b, r, ch.hi * 4, 0, POLICY);
+}
 
-// Replica rows: non-temporal stores of the rounded values.
-template <bool W>
-__device__ __forceinline__ void store_chunk(float* row, const Chunk& ch, const Packed8<F32>& x) {
-    if (W) {
-        const __amdgpu_buffer_rsrc_t r = chunk_rsrc(row, ch);
-        __builtin_amdgcn_raw_buffer_store_b128(x.r.a, r, ch.lane * 4, 0, kBufferNonTemporal);
-        __builtin_amdgcn_raw_buffer_store_b128(x.r.b, r, ch.lane * 4 + 16, 0, kBufferNonTemporal);
+template <int POLICY, bool SPLIT>
+__device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, const Chunk<SPLIT>& ch,
+                                          const Raw8<BF16>& x) {
+    if (SPLIT) {
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{x.a.x, x.a.y}, r, ch.lane * 2, 0, POLICY);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{x.a.z, x.a.w}, r, ch.hi * 2, 0, POLICY);
     } else {
-        x.template store<false>(row + ch.e0, ch.nv);
+        __builtin_amdgcn_raw_buffer_store_b128(x.a, r, ch.lane * 2, 0, POLICY);
     }
 }
 
-template <bool W>
-__device__ __forceinline__ void store_chunk(uint16_t* row, const Chunk& ch,
-                                            const Packed8<BF16>& x) {
-    if (W)
-        __builtin_amdgcn_raw_buffer_store_b128(x.r.a, chunk_rsrc(row, ch), ch.lane * 2, 0,
-                                               kBufferNonTemporal);
-    else
-        x.template store<false>(row + ch.e0, ch.nv);
+// The element-by-element form; elements past nv read as 0.
+template <bool SPLIT>
+__device__ __forceinline__ void load_elems(const float* base, const Chunk<SPLIT>& ch,
+                                           Raw8<F32>& r) {
+    uint32_t w[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w[j] = j < ch.nv ? __float_as_uint(base[ch.at(j)]) : 0u;
+    r.a = u32x4{w[0], w[1], w[2], w[3]};
+    r.b = u32x4{w[4], w[5], w[6], w[7]};
+}
+
+template <bool SPLIT>
+__device__ __forceinline__ void load_elems(const uint16_t* base, const Chunk<SPLIT>& ch,
+                                           Raw8<BF16>& r) {
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < ch.nv) w[j >> 1] |= (uint32_t)base[ch.at(j)] << (16 * (j & 1));
+    r.a = u32x4{w[0], w[1], w[2], w[3]};
+}
+
+template <bool SPLIT>
+__device__ __forceinline__ void store_elems(float* base, const Chunk<SPLIT>& ch,
+                                            const Raw8<F32>& r) {
+    const uint32_t w[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < ch.nv) base[ch.at(j)] = __uint_as_float(w[j]);
+}
+
+template <bool SPLIT>
+__device__ __forceinline__ void store_elems(uint16_t* base, const Chunk<SPLIT>& ch,
+                                            const Raw8<BF16>& r) {
+    const uint32_t w[4] = {r.a.x, r.a.y, r.a.z, r.a.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < ch.nv) base[ch.at(j)] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+}
+
+// Master, moments and aggregate: fp32, read again next step, plain policy.
+template <bool W, bool SPLIT>
+__device__ __forceinline__ void load_chunk(const float* base, const Chunk<SPLIT>& ch,
+                                           Raw8<F32>& r) {
+    if (W) load_buf<0>(chunk_rsrc(base, ch), ch, r);
+    else load_elems(base, ch, r);
+}
+
+template <bool W, bool SPLIT>
+__device__ __forceinline__ void store_chunk(float* base, const Chunk<SPLIT>& ch,
+                                            const float (&x)[8]) {
+    Raw8<F32> r;
+    pack(x, r);
+    if (W) store_buf<0>(chunk_rsrc(base, ch), ch, r);
+    else store_elems(base, ch, r);
+}
+
+// Rows of type E (gradients, replicas, last arrived contributions).
+template <class E, bool W, bool SPLIT>
+__device__ __forceinline__ void load_row(const typename E::T* row, const Chunk<SPLIT>& ch,
+                                         Raw8<E>& r) {
+    if (W) load_buf<row_policy<E, SPLIT>()>(chunk_rsrc(row, ch), ch, r);
+    else load_elems(row, ch, r);
+}
+
+template <class E, bool W, bool SPLIT>
+__device__ __forceinline__ void store_row(typename E::T* row, const Chunk<SPLIT>& ch,
+                                          const Raw8<E>& r) {
+    if (W) store_buf<row_policy<E, SPLIT>()>(chunk_rsrc(row, ch), ch, r);
+    else store_elems(row, ch, r);
 }
 
 // ---------------------------------------------------------------------------
@@ -525,11 +480,10 @@ struct RowWalk {
 // size 0.  Every turn of the ring issues the same D loads and the loop is left
 // only at the end of a turn, so the compiler waits for exactly one row before
 // each use.
-template <int D, class E, bool W, class PaceFn, class UseFn>
+template <int D, class E, bool W, bool SPLIT, class PaceFn, class UseFn>
 __device__ __forceinline__ void stream_rows(const typename E::T* rows, int64_t ld,
-                                            const Chunk& ch, RowWalk& walk, const PaceFn& pace,
-                                            const UseFn& use) {
-    const int lane = (int)threadIdx.x * kElems * (int)sizeof(typename E::T);
+                                            const Chunk<SPLIT>& ch, RowWalk& walk,
+                                            const PaceFn& pace, const UseFn& use) {
     const int bytes = ch.cv * (int)sizeof(typename E::T);
     int r[D];
     Raw8<E> b[D];
@@ -539,11 +493,10 @@ __device__ __forceinline__ void stream_rows(const typename E::T* rows, int64_t l
     const int first = r[0];
     auto issue = [&](int row, Raw8<E>& x) {
         const int at = __builtin_amdgcn_readfirstlane(row >= 0 ? row : first);
-        if (W) {
-            load_buf(row_rsrc(rows + (int64_t)at * ld + ch.c0, row >= 0 ? bytes : 0), lane, x);
-        } else {
-            load_raw<false>(rows + (int64_t)at * ld + ch.e0, ch.nv, x);
-        }
+        if (W)
+            load_buf<row_policy<E, SPLIT>()>(
+                row_rsrc(rows + (int64_t)at * ld + ch.c0, row >= 0 ? bytes : 0), ch, x);
+        else load_elems(rows + (int64_t)at * ld, ch, x);
     };
 #pragma unroll
     for (int u = 0; u < D; ++u) {
@@ -699,14 +652,13 @@ __device__ __forceinline__ float parity_invq(const AggVariant& v, int64_t k, int
 // Stale fill (Algorithm 1): every row in ascending order contributes its
 // arrived value or, if lost, its last arrived one from g_prev; arrived values
 // are written to g_prev; g = sum / n.
-template <class E, bool W, class Pace>
-__device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t ld, const Chunk& ch,
+template <class E, bool W, bool SPLIT, class Pace>
+__device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t ld,
+                                           const Chunk<SPLIT>& ch,
                                            const uint64_t* gm, int n, int K, float lam,
                                            const float (&th)[8], const AggVariant& var,
                                            bool reliable_packet, const Pace& pace,
                                            float (&g)[8]) {
-    const int64_t e0 = ch.e0;
-    const int nv = ch.nv;
 #pragma unroll
     for (int j = 0; j < 8; ++j) g[j] = 0.0f;
     if (var.kind == kEstStaleFill) {
@@ -720,7 +672,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
                 arr[u] = (uniform64(gm[row >> 6]) >> (row & 63)) & 1;
                 const typename E::T* src = arr[u] ? grads : prev;
                 pace.grad(row);
-                load_raw<W>(src + (int64_t)row * ld + e0, nv, raw[u]);
+                load_row<E, W>(src + (int64_t)row * ld, ch, raw[u]);
             }
 #pragma unroll
             for (int u = 0; u < kBatchGrad; ++u) {
@@ -729,7 +681,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
                     unpack(raw[u], x);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) g[j] += x[j];
-                    if (arr[u]) store_raw<W>(prev + (int64_t)(i0 + u) * ld + e0, nv, raw[u]);
+                    if (arr[u]) store_row<E, W>(prev + (int64_t)(i0 + u) * ld, ch, raw[u]);
                 }
             }
         }
@@ -758,7 +710,9 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
             float own[8] = {0, 0, 0, 0, 0, 0, 0, 0};
             if (sure_row >= 0) {
                 pace.grad(sure_row);
-                load8<E, W>(grads + (int64_t)sure_row * ld + e0, nv, own);
+                Raw8<E> raw;
+                load_row<E, W>(grads + (int64_t)sure_row * ld, ch, raw);
+                unpack(raw, own);
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) g[j] = (g[j] * var.invq + own[j]) / nf;
@@ -774,7 +728,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
 }
 
 // ---------------------------------------------------------------------------
-// Owner update (Section 3 step (3)), 8 elements, fp32.
+// Owner update (Section 3 step (3)), N elements, fp32.
 // ---------------------------------------------------------------------------
 struct OptParams {
     int kind;  // 0 SGD, 1 momentum, 2 Adam
@@ -782,21 +736,22 @@ struct OptParams {
     float bc1, bc2;  // 1 - beta^(t+1), rounded to fp32 on the host
 };
 
-__device__ __forceinline__ void update8(const OptParams& o, float (&th)[8], float (&m)[8],
-                                        float (&v)[8], const float (&g)[8]) {
+template <int N>
+__device__ __forceinline__ void update(const OptParams& o, float (&th)[N], float (&m)[N],
+                                       float (&v)[N], const float (&g)[N]) {
     if (o.kind == 0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) th[j] = th[j] - o.lr * g[j];
+        for (int j = 0; j < N; ++j) th[j] = th[j] - o.lr * g[j];
     } else if (o.kind == 1) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < N; ++j) {
             m[j] = o.momentum * m[j] + g[j];
             th[j] = th[j] - o.lr * m[j];
         }
     } else {
         const float a1 = 1.0f - o.beta1, a2 = 1.0f - o.beta2;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < N; ++j) {
             m[j] = o.beta1 * m[j] + a1 * g[j];
             v[j] = o.beta2 * v[j] + a2 * (g[j] * g[j]);
             const float mh = m[j] / o.bc1;
