@@ -35,6 +35,7 @@ METRIC = "aggregate+step+broadcast GB/s and % of HBM peak; N=64 7B-shard step"
 PMC_PROFILE = os.path.join(HERE, "profiles", "k_step_paced_n64_llama7b_shard_pmc.txt")
 KERNEL_SOURCES = ["paper_2507_07114_amd/csrc/kernels.hip",
                   "paper_2507_07114_amd/csrc/lossy_device.h",
+                  "paper_2507_07114_amd/csrc/flat_tile.h",
                   "paper_2507_07114_amd/csrc/kernels.h"]
 
 

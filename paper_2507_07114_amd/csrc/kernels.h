@@ -82,6 +82,7 @@ struct AggParams {
     int n;
     int64_t d, L, P;
     int cpp;  // chunks per packet (set by the launcher)
+    int slots;  // most packets of a flat tile, or 0: tiles are chunks of one packet (same)
     const void* grads;
     int64_t ld;
     const uint8_t* arrived;
@@ -95,7 +96,7 @@ struct AggParams {
 struct BcastParams {
     int n;
     int64_t d, L, P;
-    int cpp;
+    int cpp, slots;
     const float* theta;
     void* replicas;
     int64_t ld;
@@ -105,7 +106,7 @@ struct BcastParams {
 struct DriftParams {
     int n;
     int64_t d, L, P;
-    int cpp;
+    int cpp, slots;
     const void* replicas;
     int64_t ld;
     const float* theta;
@@ -117,7 +118,7 @@ struct DriftParams {
 struct FusedParams {
     int n;
     int64_t d, L, P;
-    int cpp;
+    int cpp, slots;
     uint64_t step;
     MaskSource src[2];  // [0] gradient, [1] broadcast
     uint8_t* out_g;

@@ -1,15 +1,15 @@
 // HIP kernels of the lossy step for gfx950 and their launchers.
 //
-// Work decomposition shared by every per-packet kernel: a workgroup owns a
-// chunk of one packet covering 4 KiB of each row it streams (256 threads =
-// 4 wave64s and 2048 elements for bf16 rows, 128 threads and 1024 elements
-// for fp32 rows); thread t owns elements [8t, 8t + 8) of the chunk, so each
-// row read or written is one 16-byte (bf16) or two 16-byte (fp32) accesses
-// per thread and a wavefront touches 1 KiB (bf16) or 2 KiB (fp32) of
-// contiguous HBM.
-// The masks of the packet sit in LDS as 64-bit words; loops over arrived or
-// stale rows walk the set bits with scalar (wave-uniform) control flow, so
-// a lost packet costs no memory traffic and causes no divergence.
+// Work decomposition shared by every kernel over packets: a workgroup owns a
+// tile covering 4 KiB of each row it streams (256 threads = 4 wave64s and
+// 2048 elements for bf16 rows, 128 threads and 1024 elements for fp32 rows),
+// and every row access of a wavefront is 1 KiB of contiguous HBM.  A tile is
+// a chunk of one packet, or, where packets do not fill chunks, a run of
+// consecutive elements over several packets (flat_tile.h).
+// The masks of a tile's packets sit in LDS as 64-bit words; loops over
+// arrived or stale rows walk the set bits with scalar (wave-uniform) control
+// flow, so a lost packet costs no memory traffic.
+#include "flat_tile.h"
 #include "kernels.h"
 
 #include <math.h>
@@ -265,6 +265,46 @@ __global__ __launch_bounds__(G::kPacketThreads) void k_aggregate(AggParams p) {
     else aggregate_chunk<G, false>(p, ch, s_words[0], K);
 }
 
+extern __shared__ uint64_t s_flat[];  // masks and weights of a flat tile (see FlatLds)
+
+template <class G, bool W, bool SPLIT>
+__device__ __forceinline__ void aggregate_flat_chunk(const AggParams& p, const Flat<SPLIT>& f,
+                                                     const FlatLds& lds) {
+    float th[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (p.lam != 0.0f && p.var.kind == kEstArrivedMean) {
+        bool none = false;  // some packet of this thread's elements has no contribution
+#pragma unroll
+        for (int q = 0; q < Flat<SPLIT>::Q; ++q)
+            none = none || flat_count(lds.words, f, f.slot(q)) == 0;
+        if (none) {
+            Raw8<F32> r;
+            load_chunk<W>(p.theta, f.ch, r);
+            unpack(r, th);
+        }
+    }
+    float g[8];
+    aggregate_flat<G, W>(reinterpret_cast<const typename G::T*>(p.grads), p.ld, f, lds, p.lam, th,
+                         p.var, NoPace(), g);
+    store_chunk<W>(p.g_hat, f.ch, g);
+}
+
+template <class G>
+__global__ __launch_bounds__(G::kPacketThreads) void k_aggregate_flat(AggParams p) {
+    constexpr int NT = G::kPacketThreads;
+    const auto f = flat_at<NT, G::kSplit>(blockIdx.x, p.d, p.L, p.n, p.slots);
+    const FlatLds lds(s_flat, 1, p.slots, f.nw);
+    const MaskSource src[1] = {{false, 0, 0, p.arrived, -1, nullptr}};
+    const int dirs[1] = {0};
+    flat_weights<NT>(p.var, 0, p.P, f, lds);
+    stage_flat<NT, 1>(src, f, p.P, 0, dirs, lds.words);
+    const int s = threadIdx.x;
+    if (p.counts && s < f.slots && f.starts_here(s))
+        p.counts[f.ch.k + s] = flat_count(lds.words, f, s);
+    if (f.ch.nv == 0) return;
+    if (f.ch.whole) aggregate_flat_chunk<G, true>(p, f, lds);
+    else aggregate_flat_chunk<G, false>(p, f, lds);
+}
+
 // Owner update alone: a stream of up to four vectors in and three out, bound
 // by HBM.  Each thread takes four consecutive elements, so every access is
 // one 16-byte access per lane and contiguous over the wavefront; NT threads
@@ -348,6 +388,32 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_broadcast(BcastParams p) 
     else broadcast_chunk<R, false>(p, ch, s_words[0], nw);
 }
 
+template <class R, bool W, bool SPLIT>
+__device__ __forceinline__ void broadcast_flat_chunk(const BcastParams& p, const Flat<SPLIT>& f,
+                                                     const FlatLds& lds) {
+    Raw8<F32> th_r;
+    load_chunk<W>(p.theta, f.ch, th_r);
+    float th[8];
+    unpack(th_r, th);
+    Raw8<R> r;
+    pack(th, r);
+    broadcast_flat<R, W>(reinterpret_cast<typename R::T*>(p.replicas), p.ld, f, lds.words, r,
+                         [](int) {});
+}
+
+template <class R>
+__global__ __launch_bounds__(R::kPacketThreads) void k_broadcast_flat(BcastParams p) {
+    constexpr int NT = R::kPacketThreads;
+    const auto f = flat_at<NT, R::kSplit>(blockIdx.x, p.d, p.L, p.n, p.slots);
+    const FlatLds lds(s_flat, 1, p.slots, f.nw);
+    const MaskSource src[1] = {{false, 0, 0, p.arrived, -1, nullptr}};
+    const int dirs[1] = {1};
+    stage_flat<NT, 1>(src, f, p.P, 0, dirs, lds.words);
+    if (f.ch.nv == 0) return;
+    if (f.ch.whole) broadcast_flat_chunk<R, true>(p, f, lds);
+    else broadcast_flat_chunk<R, false>(p, f, lds);
+}
+
 // Drift of one chunk over all rows, read in ascending order.
 template <class R, bool W, bool SPLIT>
 __device__ __forceinline__ void drift_chunk(const DriftParams& p, const Chunk<SPLIT>& ch, double& pair,
@@ -406,6 +472,34 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_drift(DriftParams p) {
         else drift_chunk<R, false>(p, ch, pair, range, abs_sum);
     }
     block_reduce_partial<NT>(pair, abs_sum, range, stale, 0, p.partials + blockIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *reduce_counter(p.groups) = 0u;
+}
+
+// The same over flat tiles: every row is read whatever its mask, so only the
+// count of stale packets needs to know where packets start.
+template <class R>
+__global__ __launch_bounds__(R::kPacketThreads) void k_drift_flat(DriftParams p) {
+    constexpr int NT = R::kPacketThreads;
+    __shared__ uint32_t s_stale;
+    const auto f = flat_at<NT, R::kSplit>(blockIdx.x, p.d, p.L, p.n, p.slots);
+    if (threadIdx.x == 0) s_stale = 0;
+    __syncthreads();
+    if (p.arrived) {
+        uint32_t mine = 0;
+        const int total = p.n * f.slots;
+        for (int q = threadIdx.x; q < total; q += NT) {
+            const int i = q / f.slots, s = q - i * f.slots;
+            if (f.starts_here(s)) mine += p.arrived[(int64_t)i * p.P + f.ch.k + s] == 0 ? 1u : 0u;
+        }
+        if (mine) atomicAdd(&s_stale, mine);
+    }
+    double pair = 0.0, range = 0.0, abs_sum = 0.0;
+    if (f.ch.nv > 0) {
+        if (f.ch.whole) drift_chunk<R, true>(p, f.ch, pair, range, abs_sum);
+        else drift_chunk<R, false>(p, f.ch, pair, range, abs_sum);
+    }
+    __syncthreads();
+    block_reduce_partial<NT>(pair, abs_sum, range, s_stale, 0, p.partials + blockIdx.x);
     if (blockIdx.x == 0 && threadIdx.x == 0) *reduce_counter(p.groups) = 0u;
 }
 
@@ -677,6 +771,128 @@ __device__ __forceinline__ void step_tile(const FusedParams& p, int64_t tile, co
     else step_tile_w<G, R, DRIFT, false>(p, ch, tile, pace, s_words);
 }
 
+// The same on a flat tile.
+template <class G, class R, bool DRIFT, bool W, bool SPLIT, class Pace>
+__device__ __forceinline__ void step_flat_chunk(const FusedParams& p, const Flat<SPLIT>& f,
+                                                const Pace& pace, const FlatLds& lds,
+                                                const Raw8<F32>& th_r, const Raw8<F32>& m_r,
+                                                const Raw8<F32>& v_r, double& pair, double& range,
+                                                double& abs_sum) {
+    constexpr int Q = Flat<SPLIT>::Q;
+    const Chunk<SPLIT>& ch = f.ch;
+    float th[8], mm[8], vv[8], g[8];
+    unpack(th_r, th);
+    aggregate_flat<G, W>(reinterpret_cast<const typename G::T*>(p.grads), p.ld_g, f, lds, p.lam, th,
+                         p.var, pace, g);
+    if (p.opt.kind >= 1) unpack(m_r, mm);
+    if (p.opt.kind == 2) unpack(v_r, vv);
+    update<8>(p.opt, th, mm, vv, g);
+    store_chunk<W>(p.theta, ch, th);
+    if (p.opt.kind >= 1) store_chunk<W>(p.m, ch, mm);
+    if (p.opt.kind == 2) store_chunk<W>(p.v, ch, vv);
+
+    Raw8<R> r;
+    pack(th, r);
+    typename R::T* reps = reinterpret_cast<typename R::T*>(p.replicas);
+    const uint64_t* words = lds.words + (size_t)f.cap * f.nw;
+    broadcast_flat<R, W>(reps, p.ld_r, f, words, r, [&](int row) { pace.rep(row); });
+    if (!DRIFT) return;
+    Drift8<typename StepBounds8<R>::type> acc;
+    float rv[8];
+    unpack(r, rv);
+    bool any[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) any[q] = flat_count(words, f, f.slot(q)) > 0;
+    acc.init_each([&](int j) { return f.pick(any, j); }, rv);
+    FlatWalk<SPLIT, true> stale(f, words, -1, nullptr);
+    stream_flat<FlatDepth<Pace, W>::stale, R, W>(
+        reps, p.ld_r, ch, stale, [&](int row) { pace.stale(row); },
+        [&](const Raw8<R>& raw, uint32_t elems) {
+            if (elems == 0) return;
+            float x[8];
+            unpack(raw, x);
+            // an element that arrived holds the reference and adds nothing
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = ((elems >> j) & 1u) ? x[j] : rv[j];
+            acc.add(x, rv, ch.nv);
+        });
+    acc.finish(p.n, ch.nv, pair, range);
+    abs_sum = acc.abs_sum;
+}
+
+template <class G, class R, bool DRIFT, bool W, bool SPLIT, class Pace>
+__device__ __forceinline__ void step_flat_w(const FusedParams& p, const Flat<SPLIT>& f, int64_t tile,
+                                            Pace pace, const FlatLds& lds) {
+    constexpr int NT = R::kPacketThreads;
+    const Chunk<SPLIT>& ch = f.ch;
+    Raw8<F32> th_r, m_r, v_r;
+    if (ch.nv > 0) {
+        load_chunk<W>(p.theta, ch, th_r);
+        if (p.opt.kind >= 1) load_chunk<W>(p.m, ch, m_r);
+        if (p.opt.kind == 2) load_chunk<W>(p.v, ch, v_r);
+    }
+    flat_weights<NT>(p.var, p.step, p.P, f, lds);
+    const int dirs[2] = {0, 1};
+    stage_flat<NT, 2>(p.src, f, p.P, p.step, dirs, lds.words, [&pace]() { pace.fetch(); });
+    pace.begin();
+
+    const uint64_t* bc = lds.words + (size_t)f.cap * f.nw;
+    if (p.out_g || p.out_b || p.ages) {
+        const int total = p.n * f.slots;
+        for (int q = threadIdx.x; q < total; q += NT) {
+            const int i = q / f.slots, s = q - i * f.slots;
+            if (!f.starts_here(s)) continue;
+            const int64_t at = (int64_t)i * p.P + ch.k + s;
+            const size_t word = (size_t)s * f.nw + (i >> 6);
+            const uint8_t rb = (bc[word] >> (i & 63)) & 1;
+            if (p.out_g) p.out_g[at] = (lds.words[word] >> (i & 63)) & 1;
+            if (p.out_b) p.out_b[at] = rb;
+            if (p.ages) p.ages[at] = rb ? 0 : (p.ages[at] == 0xFFFF ? 0xFFFF : p.ages[at] + 1);
+        }
+    }
+    // the first wavefront keeps the packets' books, one packet per lane
+    uint32_t stale = 0, empty = 0;
+    if (threadIdx.x < 64) {
+        const int s = threadIdx.x;
+        if (s < f.slots && f.starts_here(s)) {
+            const int K = flat_count(lds.words, f, s);
+            if (p.counts) p.counts[ch.k + s] = K;
+            if (DRIFT) {
+                stale = (uint32_t)(p.n - flat_count(bc, f, s));
+                empty = K == 0 ? 1u : 0u;
+            }
+        }
+        if (DRIFT) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                stale += __shfl_down(stale, off, 64);
+                empty += __shfl_down(empty, off, 64);
+            }
+        }
+    }
+
+    double pair = 0.0, range = 0.0, abs_sum = 0.0;
+    if (ch.nv > 0)
+        step_flat_chunk<G, R, DRIFT, W>(p, f, pace, lds, th_r, m_r, v_r, pair, range, abs_sum);
+    if (DRIFT) {
+        block_reduce_partial<NT>(pair, abs_sum, range, stale, empty, p.partials + tile);
+        if (tile == 0 && threadIdx.x == 0) *reduce_counter(p.groups) = 0u;
+    }
+}
+
+template <class G, class R, bool DRIFT, class Pace>
+__device__ __forceinline__ void step_flat(const FusedParams& p, int64_t tile, const Pace& pace) {
+    const auto f = flat_at<R::kPacketThreads, R::kSplit>(tile, p.d, p.L, p.n, p.slots);
+    const FlatLds lds(s_flat, 2, p.slots, f.nw);
+    if (f.ch.whole) step_flat_w<G, R, DRIFT, true>(p, f, tile, pace, lds);
+    else step_flat_w<G, R, DRIFT, false>(p, f, tile, pace, lds);
+}
+
+template <class G, class R, bool DRIFT>
+__global__ __launch_bounds__(R::kPacketThreads) void k_step_flat(FusedParams p) {
+    step_flat<G, R, DRIFT>(p, blockIdx.x, NoPace());
+}
+
 // One tile per workgroup.
 template <class G, class R, bool DRIFT>
 __global__ __launch_bounds__(R::kPacketThreads) void k_step_fused(FusedParams p) {
@@ -696,6 +912,22 @@ __global__ void k_pace_anchor(uint64_t margin_ticks) {
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Pace of round r of the schedule; `anchor` is a place in LDS.
+__device__ __forceinline__ ClockPace round_pace(const PaceParams& q, uint64_t r, uint64_t* anchor) {
+    ClockPace pace;
+    pace.anchor_src = &g_pace_anchor;
+    pace.anchor = anchor;
+    pace.round_start = (r * q.round) >> 8;
+    pace.off_g = q.off_g;
+    pace.off_r = q.off_r;
+    pace.off_s = q.off_s;
+    pace.dg = q.dg;
+    pace.dr = q.dr;
+    pace.ds = q.ds;
+    pace.guard = q.guard;
+    return pace;
+}
+
 // Paced step: one tile per workgroup as in k_step_fused, tile b in round
 // b / per_round, per_round no more than the workgroups the chip holds at
 // once.  Round r's row accesses follow the slot schedule anchored at
@@ -707,18 +939,16 @@ template <class G, class R, bool DRIFT>
 __global__ __launch_bounds__(R::kPacketThreads) void k_step_paced(FusedParams p, PaceParams q) {
     __shared__ uint64_t s_words[2][kMaxWords];
     __shared__ uint64_t s_anchor;  // read after the barrier that ends the mask staging
-    ClockPace pace;
-    pace.anchor_src = &g_pace_anchor;
-    pace.anchor = &s_anchor;
-    pace.round_start = (((uint64_t)blockIdx.x / (uint64_t)q.per_round) * q.round) >> 8;
-    pace.off_g = q.off_g;
-    pace.off_r = q.off_r;
-    pace.off_s = q.off_s;
-    pace.dg = q.dg;
-    pace.dr = q.dr;
-    pace.ds = q.ds;
-    pace.guard = q.guard;
+    const ClockPace pace = round_pace(q, (uint64_t)blockIdx.x / (uint64_t)q.per_round, &s_anchor);
     step_tile<G, R, DRIFT>(p, blockIdx.x, pace, s_words);
+}
+
+template <class G, class R, bool DRIFT>
+__global__ __launch_bounds__(R::kPacketThreads) void k_step_flat_paced(FusedParams p,
+                                                                       PaceParams q) {
+    __shared__ uint64_t s_anchor;
+    const ClockPace pace = round_pace(q, (uint64_t)blockIdx.x / (uint64_t)q.per_round, &s_anchor);
+    step_flat<G, R, DRIFT>(p, blockIdx.x, pace);
 }
 
 // ---------------------------------------------------------------------------
@@ -842,17 +1072,7 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_step_lean(FusedParams p, 
     for (int64_t r = 0;; ++r) {
         const int64_t tile = r * q.per_round + (int64_t)blockIdx.x;
         if (tile >= tiles) break;
-        ClockPace pace;
-        pace.anchor_src = &g_pace_anchor;
-        pace.anchor = &s_anchor;
-        pace.round_start = ((uint64_t)r * q.round) >> 8;
-        pace.off_g = q.off_g;
-        pace.off_r = q.off_r;
-        pace.off_s = q.off_s;
-        pace.dg = q.dg;
-        pace.dr = q.dr;
-        pace.ds = q.ds;
-        pace.guard = q.guard;
+        ClockPace pace = round_pace(q, (uint64_t)r, &s_anchor);
         lean_tile<G, R, DRIFT>(p, tile, pace, s_words);
         // the next tile rewrites the masks and the anchor in LDS
         __syncthreads();
@@ -930,18 +1150,57 @@ hipError_t launch_masks_ge(const GeLaunch& L, int ndir, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Chunks per packet and workgroups for a per-packet kernel of NT threads.
-template <int NT>
-static int64_t packet_grid(int64_t P, int64_t L, int* cpp) {
-    *cpp = (int)((L + NT * kElems - 1) / (NT * kElems));
-    return P * *cpp;
+// Tiles of a kernel over rows of type E: chunks of one packet each (cpp per
+// packet, slots = 0), or flat tiles (slots > 0) where a packet's chunks would
+// start off the 128-byte lines or leave much of a workgroup idle.  A chunk
+// tile's masks are wave-uniform, so it is the better one where it is full.
+// Measured, chunk tiles against flat ones (us per step, Adam with drift, p =
+// 0.1, d and N as given):
+//   off the lines (L not a multiple of 64 elements)
+//     bf16 N = 64, 16 M  L = 750: 3383 / 882   6000: 879 / 786   8184: 892 / 786
+//     bf16 N = 8, 8 M    L = 750: 419 / 97     6000: 85 / 91     20000: 84 / 91
+//     broadcast, bf16 N = 32, 8 M              6000: 114 / 92    8184: 122 / 92
+//   on the lines, by the share of the threads that a packet's chunks fill
+//     bf16 N = 64, 16 M  12%: 5960 / 916  75%: 1021 / 798  87%: 767 / 841 (L =
+//                        1792), 799 / 788 (3584)  94%: 775 / -
+//     bf16 N = 8, 8 M    12%: 279 / 103   75%: 89 / 92     87%: 86 / 93
+//     fp32 N = 64, 8 M   25%: 3102 / 827  87%: 895 / 797   94%: 842 / 800
+//     fp32 N = 16, 4 M   25%: 139 / 115   87%: 114 / 115
+//     bf16 83% (L = 5120)  N = 8, 8 M: 85 / 92   N = 32: 211 / 216   N = 64, 16 M:
+//                        913 / 784
+// The share lies at 95% for fp32 rows and at 85% for bf16 rows, 80% below 48
+// of them.  A multiple of 8 off the lines stays with chunk tiles below `few`
+// rows: 12 in a step (and in the drift pass, whose partials are the step's),
+// where little of the time is row traffic, and none in an aggregate or a
+// broadcast by itself.
+constexpr int kFewStepRows = 12;
+struct TileGrid {
+    int64_t tiles;
+    int cpp, slots;
+    size_t lds;  // dynamic LDS of a flat tile
+};
+template <class E>
+static TileGrid tile_grid(int n, int64_t d, int64_t P, int64_t L, int ndir, int few) {
+    constexpr int T = E::kPacketThreads * kElems;
+    const int percent = sizeof(typename E::T) == 4 ? 95 : (n >= 48 ? 85 : 80);
+    const int64_t cpp = (L + T - 1) / T;
+    const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
+    const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
+    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines))
+        return TileGrid{P * cpp, (int)cpp, 0, 0};
+    const int slots = flat_slots(T, L);
+    return TileGrid{(d + T - 1) / T, 0, slots, flat_lds_bytes(ndir, slots, n)};
 }
 
 template <class G>
 static void launch_aggregate_t(AggParams p, hipStream_t s) {
     constexpr int NT = G::kPacketThreads;
-    const int64_t blocks = packet_grid<NT>(p.P, p.L, &p.cpp);
-    hipLaunchKernelGGL(k_aggregate<G>, dim3((unsigned)blocks), dim3(NT), 0, s, p);
+    const TileGrid t = tile_grid<G>(p.n, p.d, p.P, p.L, 1, 0);
+    p.cpp = t.cpp;
+    p.slots = t.slots;
+    if (t.slots)
+        hipLaunchKernelGGL(k_aggregate_flat<G>, dim3((unsigned)t.tiles), dim3(NT), t.lds, s, p);
+    else hipLaunchKernelGGL(k_aggregate<G>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
 }
 
 hipError_t launch_aggregate(int gdtype, const AggParams& p, hipStream_t s) {
@@ -974,8 +1233,12 @@ hipError_t launch_shard_step(int64_t d, const OptParams& o, float* theta, float*
 template <class R>
 static void launch_broadcast_t(BcastParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
-    const int64_t blocks = packet_grid<NT>(p.P, p.L, &p.cpp);
-    hipLaunchKernelGGL(k_broadcast<R>, dim3((unsigned)blocks), dim3(NT), 0, s, p);
+    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 1, 0);
+    p.cpp = t.cpp;
+    p.slots = t.slots;
+    if (t.slots)
+        hipLaunchKernelGGL(k_broadcast_flat<R>, dim3((unsigned)t.tiles), dim3(NT), t.lds, s, p);
+    else hipLaunchKernelGGL(k_broadcast<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
 }
 
 hipError_t launch_broadcast(int rdtype, const BcastParams& p, hipStream_t s) {
@@ -987,9 +1250,12 @@ hipError_t launch_broadcast(int rdtype, const BcastParams& p, hipStream_t s) {
 template <class R>
 static int64_t launch_drift_t(DriftParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
-    const int64_t blocks = packet_grid<NT>(p.P, p.L, &p.cpp);
-    hipLaunchKernelGGL(k_drift<R>, dim3((unsigned)blocks), dim3(NT), 0, s, p);
-    return blocks;
+    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 0, kFewStepRows);
+    p.cpp = t.cpp;
+    p.slots = t.slots;
+    if (t.slots) hipLaunchKernelGGL(k_drift_flat<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
+    else hipLaunchKernelGGL(k_drift<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
+    return t.tiles;
 }
 
 hipError_t launch_drift(int rdtype, const DriftParams& p, int n, int64_t d, int have_master,
@@ -1101,9 +1367,12 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     int dev = 0, cus = 0;
     double tick_hz = 0.0;
     if (hipGetDevice(&dev) != hipSuccess || !device_info(dev, &cus, &tick_hz)) return false;
-    static int occupancy[kMaxDevices], occupancy_lean[kMaxDevices];
-    const int per_cu = lean ? resident_per_cu(dev, k_step_lean<G, R, DRIFT>, NT, occupancy_lean)
-                            : resident_per_cu(dev, k_step_paced<G, R, DRIFT>, NT, occupancy);
+    static int occupancy[kMaxDevices], occupancy_lean[kMaxDevices], occupancy_flat[kMaxDevices];
+    // (a flat tile's LDS, under 9 KiB, never limits the occupancy)
+    const int per_cu =
+        p.slots ? resident_per_cu(dev, k_step_flat_paced<G, R, DRIFT>, NT, occupancy_flat)
+        : lean  ? resident_per_cu(dev, k_step_lean<G, R, DRIFT>, NT, occupancy_lean)
+                : resident_per_cu(dev, k_step_paced<G, R, DRIFT>, NT, occupancy);
     const int k = st.overlap < 1 ? 1 : (st.overlap > 2 ? 2 : st.overlap);
     const int res = st.resident < k ? k : st.resident;
     // A round of an fp32-row kernel is at most kPaceMaxRoundTiles tiles (a
@@ -1128,7 +1397,9 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     const double qg = h.q_g < 0.0 ? 0.0 : (h.q_g > 1.0 ? 1.0 : h.q_g);
     const double qb = h.q_b < 0.0 ? 0.0 : (h.q_b > 1.0 ? 1.0 : h.q_b);
     const double n = (double)p.n;
-    const double dg = g * row_g * qg * fp;
+    // stale fill reads every row and writes the arrived ones to g_prev
+    const bool fill = p.var.kind == kEstStaleFill;
+    const double dg = g * row_g * (fill ? 1.0 + qg : qg) * fp;
     const double dr = g * row_r * qb * fp;
     const double ds = DRIFT ? g * row_r * (1.0 - qb) * fp : 0.0;
     const double off_g = st.lead_us * us + g * state * fp;
@@ -1166,7 +1437,10 @@ template <class G, class R, bool DRIFT>
 static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     FusedParams pp = p;
-    const int64_t tiles = packet_grid<NT>(pp.P, pp.L, &pp.cpp);
+    const TileGrid t = tile_grid<R>(pp.n, pp.d, pp.P, pp.L, 2, kFewStepRows);
+    const int64_t tiles = t.tiles;
+    pp.cpp = t.cpp;
+    pp.slots = t.slots;
     PaceParams q;
     int64_t grid = 0;
     uint64_t margin = 0;
@@ -1187,7 +1461,7 @@ static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStre
         if (dir == 1 && pm.out_b == pm.pre[1]) pm.out_b = nullptr;
     }
     // The persistent form takes the plain configuration only (see k_step_lean).
-    bool lean = st.persistent && pm.var.kind == kEstArrivedMean && !pm.ages && !pm.out_g &&
+    bool lean = st.persistent && !t.slots && pm.var.kind == kEstArrivedMean && !pm.ages && !pm.out_g &&
                 !pm.out_b && pm.L % 8 == 0 && pm.d % 8 == 0;
     for (int dir = 0; dir < 2; ++dir)
         lean = lean && !pm.src[dir].draw && pm.src[dir].owner < 0 && !pm.src[dir].reliable;
@@ -1195,12 +1469,18 @@ static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStre
         if (njobs && launch_masks_bernoulli_jobs(pm.n, pm.P, pm.step, jobs, njobs, s) != hipSuccess)
             return -1;
         hipLaunchKernelGGL(k_pace_anchor, dim3(1), dim3(64), 0, s, margin);
-        if (lean)
+        if (t.slots)
+            hipLaunchKernelGGL((k_step_flat_paced<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT),
+                               t.lds, s, pm, q);
+        else if (lean)
             hipLaunchKernelGGL((k_step_lean<G, R, DRIFT>), dim3((unsigned)grid), dim3(NT), 0, s,
                                pm, q, tiles);
         else
             hipLaunchKernelGGL((k_step_paced<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), 0, s,
                                pm, q);
+    } else if (t.slots) {
+        hipLaunchKernelGGL((k_step_flat<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), t.lds, s,
+                           pp);
     } else {
         hipLaunchKernelGGL((k_step_fused<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), 0, s, pp);
     }

@@ -823,15 +823,20 @@ struct Drift8 {
     B b;
     double abs_sum;
 
-    __device__ __forceinline__ void init(bool any_equal_ref, const float (&r)[8]) {
+    // equal_ref(j): some row holds the reference itself at element j.
+    template <class Any>
+    __device__ __forceinline__ void init_each(const Any& equal_ref, const float (&r)[8]) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
+            const bool any = equal_ref(j);
             s1[j] = 0.0;
             s2[j] = 0.0;
-            b.init(j, any_equal_ref ? r[j] : -__builtin_inff(),
-                   any_equal_ref ? r[j] : __builtin_inff());
+            b.init(j, any ? r[j] : -__builtin_inff(), any ? r[j] : __builtin_inff());
         }
         abs_sum = 0.0;
+    }
+    __device__ __forceinline__ void init(bool any_equal_ref, const float (&r)[8]) {
+        init_each([&](int) { return any_equal_ref; }, r);
     }
     __device__ __forceinline__ void add(const float (&x)[8], const float (&r)[8], int nv) {
 #pragma unroll

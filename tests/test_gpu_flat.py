@@ -1,0 +1,166 @@
+"""Flat tiles: packet lengths that do not fill the chunks of one packet.
+
+A tile then covers consecutive elements of several packets, with each
+thread's elements in up to two (bf16 rows) or four (fp32 rows) of them.  The
+lengths here put packet borders inside a thread's vector, at a wavefront's and
+a tile's edge, and one packet over many tiles; worker counts cross the 32- and
+64-row mask words and the ballots that hold several packets.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_07114_amd as ll
+import workloads as wl
+
+import parity
+from test_gpu_fused import _bit_equal, _snapshot, _stagewise
+from test_gpu_fuzz import OPTS, test_random_configuration as check_configuration
+from test_gpu_pacing import _step, restore_pacing  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+BERN = dict(kind=wl.BERNOULLI, p=0.3)
+GE = dict(kind=wl.GILBERT_ELLIOTT, p_gb=0.2, p_bg=0.3, loss_good=0.05, loss_bad=0.7)
+
+
+def _case(case, n, packet, d, gdtype, opt, loss=BERN, est="arrived_mean", owner=-1,
+          reliable=False, parity=0, lam=0.0):
+    return dict(case=case, n=n, packet=packet, d=d, gdtype=gdtype, opt=opt, loss=loss, est=est,
+                owner=owner, reliable=reliable, parity=parity, lam=lam)
+
+
+CASES = [
+    # the shortest flat packets (33 per tile), and the longest that are not
+    _case(2000, 16, 64, 9_001, wl.BF16, "adam"),
+    _case(2001, 3, 63, 4_001, wl.BF16, "adam"),
+    _case(2002, 1, 65, 2_048, wl.F32, "sgd"),
+    # Ethernet payloads; owner, reliable and parity packets; empty packets
+    _case(2003, 16, 750, 20_011, wl.BF16, "adam", owner=5, reliable=True, parity=4),
+    _case(2004, 33, 375, 10_007, wl.F32, "momentum",
+          dict(kind=wl.BERNOULLI, p=0.97), lam=0.1),
+    _case(2005, 2, 2250, 4_096, wl.BF16, "sgd", dict(kind=wl.BERNOULLI, p=1.0), lam=0.1),
+    # Horvitz-Thompson: weights that differ between the packets of a tile
+    _case(2006, 20, 100, 6_001, wl.BF16, "adam", est="horvitz_thompson", owner=19, reliable=True,
+          parity=3),
+    _case(2007, 70, 333, 6_002, wl.F32, "momentum", GE, est="horvitz_thompson", owner=66,
+          reliable=True),
+    # stale fill: a vector half from the arrived row, half from the last one
+    _case(2008, 31, 750, 12_345, wl.BF16, "momentum", est="stale_fill"),
+    _case(2009, 65, 129, 5_003, wl.F32, "sgd", GE, est="stale_fill", reliable=True),
+    # one element more and less than a tile, and a packet of several tiles
+    _case(2010, 8, 2047, 16_384, wl.BF16, "adam"),
+    _case(2011, 64, 1025, 16_385, wl.F32, "adam", GE),
+    _case(2012, 130, 8191, 30_001, wl.BF16, "adam"),
+    _case(2013, 1024, 200, 3_000, wl.F32, "adam", owner=1000),
+    # lengths a multiple of 8 that fill few threads of a chunk
+    _case(2014, 64, 256, 12_288, wl.BF16, "adam"),
+    _case(2015, 5, 264, 7_000, wl.F32, "momentum", est="stale_fill"),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"case{c['case']}")
+def test_flat_step_matches_the_oracle(cfg):
+    check_configuration(cfg)
+
+
+@pytest.mark.parametrize("name,n,d,L,pad", [
+    ("n8_d16m_bf16_adam", 8, 40_961, 750, 0),
+    ("n8_d16m_bf16_adam", 200, 9_001, 256, 8),
+    ("n64_d48m_f32_sgd_drift", 64, 20_005, 375, 4),
+    ("n16_d256m_f32_ge_momentum", 17, 30_720, 2250, 0),
+])
+def test_flat_step_equals_stagewise(name, n, d, L, pad):
+    w = wl.scaled(wl.WORKLOADS[name], n=n, d=d, packet=L)
+    a, b = parity.DeviceState(w, pad=pad), parity.DeviceState(w, pad=pad)
+    for t in range(2):
+        print(f"flat {name} n={n} d={d} L={L} step {t}", flush=True)
+        wl.draw_grads(w, t, device=DEV, ld=a.ld, out=a.grads)
+        b.grads.copy_(a.grads)
+        a.fused(t)
+        _stagewise(b, t)
+        sa, sb = _snapshot(a), _snapshot(b)
+        sa["drift"]["empty_packets"] = sb["drift"]["empty_packets"] = 0
+        assert sa["drift"] == sb["drift"], (sa["drift"], sb["drift"])
+        for k in sa:
+            if k != "drift":
+                assert _bit_equal(sa[k], sb[k]), f"step {t}: {k} differs"
+
+
+@pytest.mark.parametrize("name,n,d,L", [
+    ("n64_llama7b_shard_bf16_adam", 64, 2048 * 2600 + 1009, 750),
+    ("n64_d48m_f32_sgd_drift", 40, 1024 * 5000 + 13, 1500),
+])
+@pytest.mark.parametrize("masks_out,drift", [(True, True), (False, False)])
+def test_flat_paced_step_is_bit_identical_to_unpaced(name, n, d, L, masks_out, drift,
+                                                     restore_pacing):  # noqa: F811
+    w = wl.scaled(wl.WORKLOADS[name], n=n, d=d, packet=L)
+    a, b = parity.DeviceState(w), parity.DeviceState(w)
+    for t in range(2):
+        print(f"flat paced {name} n={n} L={L} step {t}", flush=True)
+        wl.draw_grads(w, t, device=DEV, ld=a.ld, out=a.grads)
+        b.grads.copy_(a.grads)
+        ll.ll_set_pacing("always")
+        _step(a, t, masks_out=masks_out, drift=drift, workspace=True)
+        ll.ll_set_pacing("never")
+        _step(b, t, masks_out=masks_out, drift=drift, workspace=True)
+        sa, sb = _snapshot(a), _snapshot(b)
+        assert not drift or sa["drift"] == sb["drift"], (sa["drift"], sb["drift"])
+        for k in sa:
+            if k != "drift" and (masks_out or not k.startswith("arrived")):
+                assert _bit_equal(sa[k], sb[k]), f"step {t}: {k} differs"
+
+
+@pytest.mark.parametrize("gdtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("est", ["arrived_mean", "horvitz_thompson", "stale_fill"])
+def test_flat_aggregate_stage(est, gdtype):
+    """lossy_aggregate alone: lost elements hold NaN and are never used."""
+    n, d, L = 37, 10_007, 333
+    P = -(-d // L)
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    arrived = (torch.rand((n, P), generator=gen, device=DEV) < 0.6).to(torch.uint8)
+    arrived[:, 3] = 0
+    reliable = torch.zeros(P, dtype=torch.uint8, device=DEV)
+    reliable[5::7] = 1
+    arrived[:, 5::7] = 1
+    arrived[2] = 1
+    owner = 2 if est == "horvitz_thompson" else -1
+    if owner < 0:
+        arrived[2, 3] = 0
+    ld = -(-d // 8) * 8
+    here = arrived.bool().repeat_interleave(L, 1)[:, :d]
+    g = torch.full((n, ld), float("nan"), device=DEV, dtype=gdtype)
+    vals = torch.randn((n, d), generator=gen, device=DEV).to(gdtype)
+    g[:, :d] = torch.where(here, vals, g[:, :d])
+    prev0 = torch.randn((n, ld), generator=gen, device=DEV).to(gdtype)
+    prev = prev0.clone() if est == "stale_fill" else None
+    theta = torch.randn(d, generator=gen, device=DEV)
+    g_hat = torch.zeros(d, device=DEV)
+    counts = torch.zeros(P, dtype=torch.int32, device=DEV)
+    e = ll.ext(est, owner=owner, reliable=reliable, g_prev=prev,
+               arrival_prob=0.6 if est == "horvitz_thompson" else 0.0)
+    lam = 0.25 if est == "arrived_mean" else 0.0
+    ll.lossy_aggregate(g, arrived, d=d, packet=L, g_hat=g_hat, counts=counts, ext=e,
+                       fallback_lambda=lam, theta=theta)
+    torch.cuda.synchronize()
+    x = torch.where(here, vals.double(), 0.0)
+    K = arrived.sum(0, dtype=torch.int32)
+    assert torch.equal(counts, K)
+    k = K.repeat_interleave(L)[:d].double()
+    if est == "arrived_mean":
+        want = torch.where(k > 0, x.sum(0) / k.clamp(min=1), lam * theta.double())
+    elif est == "horvitz_thompson":
+        sure = reliable.bool().repeat_interleave(L)[:d]
+        w = np.float32(1.0 / 0.6).item()
+        wt = torch.where(sure, 1.0, torch.tensor(w, dtype=torch.float64, device=DEV))
+        lossy = x.clone()
+        lossy[owner] = 0
+        want = (lossy.sum(0) * wt + x[owner]) / n
+    else:
+        mix = torch.where(here, vals, prev0[:, :d])
+        want = mix.double().sum(0) / n
+        assert torch.equal(prev[:, :d], mix) and torch.equal(prev[:, d:], prev0[:, d:])
+    # a sequential fp32 sum of n terms of either sign and two more roundings
+    tol = 1e-5 * x.abs().sum(0).clamp(min=1.0)
+    assert ((g_hat.double() - want).abs() <= tol).all()
