@@ -275,7 +275,8 @@ __device__ __forceinline__ uint32_t pair_on(uint32_t e, int j) {
 __device__ __forceinline__ void keep_elems(uint32_t e, Raw8<BF16>& r) {
     r.a &= u32x4{pair_on(e, 0), pair_on(e, 2), pair_on(e, 4), pair_on(e, 6)};
 }
-__device__ __forceinline__ bool some_elems(uint32_t e) { return e != 0u && e != 0xFFu; }
+// some but not all of the 8
+__device__ __forceinline__ bool some_elems(uint32_t e) { return e - 1u < 0xFEu; }
 
 __device__ __forceinline__ void merge(const Raw8<F32>& y, Raw8<F32>& x) {
     x.a |= y.a;

@@ -1172,7 +1172,11 @@ hipError_t launch_masks_ge(const GeLaunch& L, int ndir, hipStream_t s) {
 // of them.  A multiple of 8 off the lines stays with chunk tiles below `few`
 // rows: 12 in a step (and in the drift pass, whose partials are the step's),
 // where little of the time is row traffic, and none in an aggregate or a
-// broadcast by itself.
+// broadcast by itself.  And a multiple of 8 stays with chunk tiles as long as
+// they are so few that most run at once: then the time is one tile's, and a
+// flat tile's code is the longer one (N = 64 bf16, L = 256: 0.2 M 30 / 49 with
+// 782 chunk tiles, 0.8 M 85 / 63 with 3125; N = 16: 20 / 23 and 46 / 27; fp32
+// N = 64, whose workgroups are half as large: 31 / 53 and 92 / 97).
 constexpr int kFewStepRows = 12;
 struct TileGrid {
     int64_t tiles;
@@ -1186,7 +1190,8 @@ static TileGrid tile_grid(int n, int64_t d, int64_t P, int64_t L, int ndir, int 
     const int64_t cpp = (L + T - 1) / T;
     const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
     const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
-    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines))
+    const bool small = L % 8 == 0 && P * cpp <= (sizeof(typename E::T) == 4 ? 4096 : 1024);
+    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small)
         return TileGrid{P * cpp, (int)cpp, 0, 0};
     const int slots = flat_slots(T, L);
     return TileGrid{(d + T - 1) / T, 0, slots, flat_lds_bytes(ndir, slots, n)};

@@ -33,7 +33,7 @@ def _case(case, n, packet, d, gdtype, opt, loss=BERN, est="arrived_mean", owner=
 
 CASES = [
     # the shortest flat packets (33 per tile), and the longest that are not
-    _case(2000, 16, 64, 9_001, wl.BF16, "adam"),
+    _case(2000, 3, 64, 70_001, wl.BF16, "adam"),
     _case(2001, 3, 63, 4_001, wl.BF16, "adam"),
     _case(2002, 1, 65, 2_048, wl.F32, "sgd"),
     # Ethernet payloads; owner, reliable and parity packets; empty packets
@@ -53,10 +53,14 @@ CASES = [
     _case(2010, 8, 2047, 16_384, wl.BF16, "adam"),
     _case(2011, 64, 1025, 16_385, wl.F32, "adam", GE),
     _case(2012, 130, 8191, 30_001, wl.BF16, "adam"),
-    _case(2013, 1024, 200, 3_000, wl.F32, "adam", owner=1000),
-    # lengths a multiple of 8 that fill few threads of a chunk
-    _case(2014, 64, 256, 12_288, wl.BF16, "adam"),
-    _case(2015, 5, 264, 7_000, wl.F32, "momentum", est="stale_fill"),
+    _case(2013, 1024, 204, 3_000, wl.F32, "adam", owner=1000),
+    # lengths a multiple of 8, flat from 1025 (bf16) or 4097 (fp32) chunk tiles
+    # on and chunks up to there
+    _case(2014, 9, 256, 256 * 1025 - 200, wl.BF16, "adam"),
+    _case(2015, 9, 256, 256 * 1024, wl.BF16, "adam"),
+    _case(2016, 2, 72, 72 * 4097 - 5, wl.F32, "momentum", est="stale_fill"),
+    # off the 128-byte lines, flat from 12 rows on in a step
+    _case(2017, 12, 6000, 400_001, wl.BF16, "sgd"),
 ]
 
 
@@ -67,9 +71,11 @@ def test_flat_step_matches_the_oracle(cfg):
 
 @pytest.mark.parametrize("name,n,d,L,pad", [
     ("n8_d16m_bf16_adam", 8, 40_961, 750, 0),
-    ("n8_d16m_bf16_adam", 200, 9_001, 256, 8),
+    ("n8_d16m_bf16_adam", 200, 9_001, 250, 8),
     ("n64_d48m_f32_sgd_drift", 64, 20_005, 375, 4),
     ("n16_d256m_f32_ge_momentum", 17, 30_720, 2250, 0),
+    # broadcast and aggregate alone on flat tiles, the step on chunks
+    ("n8_d16m_bf16_adam", 8, 1_200_000, 1928, 0),
 ])
 def test_flat_step_equals_stagewise(name, n, d, L, pad):
     w = wl.scaled(wl.WORKLOADS[name], n=n, d=d, packet=L)
