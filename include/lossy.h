@@ -353,12 +353,14 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * is not kept and the speed falls back towards the unpaced one; too slow, the
  * step runs at the set rate.
  *   mode         LL_PACE_AUTO (default): paced where it was measured to pay,
- *                steps with at least 32 workers and at least 8 rounds (few
- *                workers break even or lose); LL_PACE_ALWAYS; LL_PACE_NEVER.
+ *                by the number of workers and of rounds (bf16 rows: from 64
+ *                workers and 3 rounds or 32 workers and 8 rounds; fp32 rows:
+ *                48 and 8, 32 and 16, or 12 and 24); LL_PACE_ALWAYS;
+ *                LL_PACE_NEVER.
  *                A round takes every resident workgroup place (bf16
- *                rows) or at most 1024 tiles (fp32 rows, 4 MiB of a row
- *                per slot).
- *   bytes_per_s  rate the slots are laid out for (default 6.3e12), for
+ *                rows) or half of them, at most 1024 tiles (fp32 rows, 4 MiB
+ *                of a row per slot).
+ *   bytes_per_s  rate the slots are laid out for (default 6.7e12), for
  *                steps whose replica rows are bf16.
  *   gap_us       time between the last gradient slot and the first replica
  *                slot, besides the master and moment writes (default 2).
@@ -371,7 +373,10 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *                rounds start half a round apart, so one round's gradient
  *                sweep runs beside the previous round's replica sweep and
  *                each round's lead and gap are covered by the other's
- *                streams (two mixed streams: measured to hold about 6.0e12).
+ *                streams.  Steps with fp32 replica rows always stream two
+ *                (except with `persistent`), and take 0.4 of gap_us, lead_us
+ *                and tail_us; bf16 steps of at least 64 workers and at most
+ *                10 rounds take half of them.
  *   resident     rounds sharing the workgroup places the chip holds at once
  *                (overlap..4; default 1): a round has headroom / resident of
  *                them, and rounds start no closer than a round's length /
@@ -390,7 +395,7 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *   bytes_per_s_f32  the same for steps whose replica rows are fp32 (their
  *                workgroups are 128 threads with two loads per row each;
  *                measured to keep their schedule at a lower rate; default
- *                5.9e12).
+ *                6.4e12).
  * A workgroup that starts behind its round (its place freed late) issues the
  * rows whose slots have passed at once and then keeps the round's slots.
  * The setting is process-wide and read at each call.  A paced step enqueues,

@@ -152,18 +152,22 @@ struct PaceParams {
     uint64_t guard;                // longest wait, ticks
 };
 
-// Pacing modes and defaults: auto paces steps of at least kPaceMinRows rows
-// spanning at least kPaceMinRounds rounds (of at most kPaceMaxRoundTiles
-// tiles for fp32 rows); the schedule is laid out for kDefaultPaceRate bytes/s
-// (kDefaultPaceRateF32 for steps with fp32 replica rows) with
+// Pacing modes and defaults: the schedule is laid out for kDefaultPaceRate
+// bytes/s (kDefaultPaceRateF32 for steps with fp32 replica rows) with
 // kDefaultPaceGapUs between the gradient and replica sweeps, and starts
-// kPaceMarginUs after the anchor is written.
+// kPaceMarginUs after the anchor is written.  The rates, on three cards (rows
+// loaded non-temporally; N = 64, kept in every one of 20 to 80 steps in a row
+// unless marked):
+//   bf16 rows, 105 M  6.3e12 4888 us, 6.6e12 4685, 6.7e12 4622, 6.8e12 4560,
+//                     6.9e12 4580-4720 (slips), 7.0e12 5300 (never kept)
+//   fp32 rows, 48 M   one round streaming: 5.9e12 4696, 6.5e12 4336, 6.7e12
+//                     4380 (slips); two: 6.2e12 4497, 6.4e12 4103 with 0.4 of
+//                     the allowances, 6.6e12 3983 (25 M: slips)
 enum { kPaceAuto = 0, kPaceAlways = 1, kPaceNever = 2 };
-constexpr int64_t kPaceMinRounds = 8;
-constexpr int kPaceMinRows = 32;
-constexpr int64_t kPaceMaxRoundTiles = 1024;
-constexpr double kDefaultPaceRate = 6.3e12;
-constexpr double kDefaultPaceRateF32 = 5.9e12;
+constexpr int64_t kPaceMaxRoundTiles = 1024;  // of fp32-row kernels
+constexpr double kPaceF32Allowance = 0.4;
+constexpr double kDefaultPaceRate = 6.7e12;
+constexpr double kDefaultPaceRateF32 = 6.4e12;
 constexpr double kDefaultPaceGapUs = 2.0;
 constexpr double kDefaultPaceLeadUs = 4.0;
 constexpr int kDefaultPaceOverlap = 1;

@@ -1327,6 +1327,27 @@ int resident_per_cu(int dev, K kernel, int threads, int (&table)[kMaxDevices]) {
     }
     return table[dev] > 0 ? table[dev] : 0;
 }
+
+// Whether LL_PACE_AUTO paces a step of n rows in `rounds` rounds.  Many rows
+// gain most: unpaced, the chip reads pieces of all of them at once.  Few rounds
+// lose the start and the end of the schedule, and rows of up to 64 MB (16
+// rounds of fp32 rows, 13 of bf16 ones) are served better unpaced than longer
+// ones.  Steps with drift, p = 0.1, unpaced / paced, us:
+//   fp32 rows  N = 64: 4 M 404 / 425, 8 M (8 rounds) 789 / 756, 48 M 4728 / 4103
+//              N = 32: 8 M 400 / 413, 16 M (16) 768 / 764, 25 M 1314 / 1150
+//              N = 24: 16 M 577 / 602, 33 M (32) 1322 / 1220
+//              N = 16: 16 M 387 / 439, 33 M 925 / 856;  N = 8: 33 M 521 / 525
+//   bf16 rows  N = 96: 3 M 221 / 238, 8 M 586 / 530
+//              N = 64: 3 M (2 rounds) 153 / 168, 8 M (4) 397 / 366, 13 M 703 / 655,
+//                      105 M 5520 / 4622
+//              N = 48: 13 M (6) 532 / 525, 33 M (13) 1311 / 1170
+//              N = 32: 17 M (7) 404 / 448, 33 M (13) 926 / 866
+//              N = 16: 100 M 1620 / 1645
+bool pace_pays(bool f32_rows, int n, int64_t rounds) {
+    if (f32_rows)
+        return (n >= 48 && rounds >= 8) || (n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24);
+    return (n >= 64 && rounds >= 3) || (n >= 32 && rounds >= 8);
+}
 }  // namespace
 
 PaceSetting get_pace_setting() {
@@ -1349,8 +1370,17 @@ void set_pace_setting(const PaceSetting& st) {
     g_pace_rate_f32.store(st.bytes_per_s_f32);
 }
 
-// Lay out the schedule of a paced step with `tiles` tiles, or return false
-// to run it unpaced.  `overlap` rounds stream at once, each covering *grid
+// What one tile of a paced kernel is expected to move: bytes per row slot of
+// each sweep, and of master and moments before and after the first sweep.
+struct PaceTile {
+    int n;
+    double grad, rep, stale;
+    double in, out;
+};
+
+// Lay out the schedule of a paced kernel with `tiles` tiles, `per_cu`
+// workgroups of it resident per compute unit, or return false to run it
+// unpaced.  `overlap` rounds stream at once, each covering *grid
 // adjacent tiles (`resident` rounds fill at most kPaceHeadroom of the
 // resident workgroup places; rounds are balanced) and laid out for its
 // share, rate / overlap, of the bandwidth.  A round is: a
@@ -1361,54 +1391,37 @@ void set_pace_setting(const PaceSetting& st) {
 // round's share.  Rounds start round / overlap apart, so with two in flight
 // one round's gradient sweep runs beside the previous round's replica sweep
 // and each round's lead, gap and tail are covered by the other's streams.
-template <class G, class R, bool DRIFT>
-static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, const PaceHint& h,
-                      int64_t tiles, PaceParams* q, int64_t* grid, uint64_t* margin) {
-    constexpr int NT = R::kPacketThreads;
-    // Steps with fp32 replica rows (128-thread workgroups, two loads per row
-    // and thread) keep their schedule at a lower rate than bf16 rows.
-    const double rate = sizeof(typename R::T) == 4 ? st.bytes_per_s_f32 : st.bytes_per_s;
-    if (st.mode == kPaceNever || !(rate > 0.0) || tiles <= 0) return false;
-    int dev = 0, cus = 0;
-    double tick_hz = 0.0;
-    if (hipGetDevice(&dev) != hipSuccess || !device_info(dev, &cus, &tick_hz)) return false;
-    static int occupancy[kMaxDevices], occupancy_lean[kMaxDevices], occupancy_flat[kMaxDevices];
-    // (a flat tile's LDS, under 9 KiB, never limits the occupancy)
-    const int per_cu =
-        p.slots ? resident_per_cu(dev, k_step_flat_paced<G, R, DRIFT>, NT, occupancy_flat)
-        : lean  ? resident_per_cu(dev, k_step_lean<G, R, DRIFT>, NT, occupancy_lean)
-                : resident_per_cu(dev, k_step_paced<G, R, DRIFT>, NT, occupancy);
-    const int k = st.overlap < 1 ? 1 : (st.overlap > 2 ? 2 : st.overlap);
+static bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per_cu,
+                        const PaceTile& w, int64_t tiles, int cus, double tick_hz, PaceParams* q,
+                        int64_t* grid, uint64_t* margin) {
+    // Rounds of fp32-row kernels hold half of the 2048 places (one row slot
+    // streams 4 MiB; rounds of all places were measured slower), so the
+    // other half takes the next round while one streams: two rounds stream at
+    // once, and since each covers the other's lead, gap and tail, 0.4 of
+    // those is enough.  Rounds of bf16-row kernels take every place (1280
+    // with drift, 1536 without): two rounds at once fall behind their
+    // schedule there.
+    const bool pair = f32_rows && !lean;
+    const double rate = f32_rows ? st.bytes_per_s_f32 : st.bytes_per_s;
+    const int k = st.overlap > 1 || pair ? 2 : 1;
     const int res = st.resident < k ? k : st.resident;
-    // A round of an fp32-row kernel is at most kPaceMaxRoundTiles tiles (a
-    // row slot streams 4 MiB): rounds of every resident place of those
-    // kernels (2048 tiles) were measured slower than rounds of half of them.
-    // Rounds of the bf16-row kernels take every place (1280 with drift,
-    // 1536 without): capped at 1024, the next round's workgroups start early
-    // in the spare places and the schedule is not kept.
     int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
-    if (sizeof(typename R::T) == 4 && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
+    if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
     if (gmax < 1) return false;
     const int64_t rounds = (tiles + gmax - 1) / gmax;
-    // Auto: only where pacing was measured to pay, many rows (the N = 64
-    // steps gain 5-10%); a few rows break even or lose.
-    if (st.mode == kPaceAuto && (rounds < kPaceMinRounds || p.n < kPaceMinRows)) return false;
+    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w.n, rounds)) return false;
     const int64_t g = (tiles + rounds - 1) / rounds;
-    const double row_g = (double)NT * kElems * sizeof(typename G::T);
-    const double row_r = (double)NT * kElems * sizeof(typename R::T);
-    const double state = (double)NT * kElems * 4.0 * (p.opt.kind + 1);
-    const double fp = 256.0 * tick_hz * k / rate;  // 1/256 ticks per byte of a round
-    const double us = 1e-6 * tick_hz * 256.0;                 // 1/256 ticks per microsecond
-    const double qg = h.q_g < 0.0 ? 0.0 : (h.q_g > 1.0 ? 1.0 : h.q_g);
-    const double qb = h.q_b < 0.0 ? 0.0 : (h.q_b > 1.0 ? 1.0 : h.q_b);
-    const double n = (double)p.n;
-    // stale fill reads every row and writes the arrived ones to g_prev
-    const bool fill = p.var.kind == kEstStaleFill;
-    const double dg = g * row_g * (fill ? 1.0 + qg : qg) * fp;
-    const double dr = g * row_r * qb * fp;
-    const double ds = DRIFT ? g * row_r * (1.0 - qb) * fp : 0.0;
-    const double off_g = st.lead_us * us + g * state * fp;
-    const double off_r = off_g + n * dg + g * state * fp + st.gap_us * us;
+    const double fp = 256.0 * tick_hz * k / rate;             // 1/256 ticks per byte of a round
+    // A short schedule of many rows is kept with half the allowances (N = 64
+    // bf16: 8 M 380 -> 365 us, 20 M, 8 rounds, 899 -> 866); over 13 rounds and
+    // more a late round is not made good any more (105 M, 41 rounds: 4622 us
+    // with all of them, 5480 with half).
+    const double allow = pair ? kPaceF32Allowance : (w.n >= 64 && rounds <= 10 ? 0.5 : 1.0);
+    const double us = 1e-6 * tick_hz * 256.0 * allow;         // 1/256 ticks per allowed microsecond
+    const double n = (double)w.n;
+    const double dg = g * w.grad * fp, dr = g * w.rep * fp, ds = g * w.stale * fp;
+    const double off_g = st.lead_us * us + g * w.in * fp;
+    const double off_r = off_g + n * dg + g * w.out * fp + st.gap_us * us;
     const double off_s = off_r + n * dr;
     // A round's workgroups leave a little after its last slot: the last rows
     // they read must arrive and the drift partial be folded.
@@ -1419,7 +1432,7 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     // sharing the resident places (length / res).  With k = 2 and res = 3
     // the lead, gap and tail of each round are covered by the other rounds'
     // streams.
-    const double stream = n * (dg + dr + ds) + 2.0 * g * state * fp;
+    const double stream = n * (dg + dr + ds) + g * (w.in + w.out) * fp;
     const double spacing = stream / k > length / res ? stream / k : length / res;
     if (!(length < 1e15)) return false;
     q->per_round = g;
@@ -1434,6 +1447,36 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     q->guard = 2 * ((uint64_t)length >> 8) + 2 * *margin + 1;
     *grid = g;
     return true;
+}
+
+// The schedule of a fused step.
+template <class G, class R, bool DRIFT>
+static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, const PaceHint& h,
+                      int64_t tiles, PaceParams* q, int64_t* grid, uint64_t* margin) {
+    constexpr int NT = R::kPacketThreads;
+    constexpr bool kF32Rows = sizeof(typename R::T) == 4;
+    if (st.mode == kPaceNever || tiles <= 0) return false;
+    int dev = 0, cus = 0;
+    double tick_hz = 0.0;
+    if (hipGetDevice(&dev) != hipSuccess || !device_info(dev, &cus, &tick_hz)) return false;
+    static int occupancy[kMaxDevices], occupancy_lean[kMaxDevices], occupancy_flat[kMaxDevices];
+    // (a flat tile's LDS, under 9 KiB, never limits the occupancy)
+    const int per_cu =
+        p.slots ? resident_per_cu(dev, k_step_flat_paced<G, R, DRIFT>, NT, occupancy_flat)
+        : lean  ? resident_per_cu(dev, k_step_lean<G, R, DRIFT>, NT, occupancy_lean)
+                : resident_per_cu(dev, k_step_paced<G, R, DRIFT>, NT, occupancy);
+    const double row_g = (double)NT * kElems * sizeof(typename G::T);
+    const double row_r = (double)NT * kElems * sizeof(typename R::T);
+    const double qg = h.q_g < 0.0 ? 0.0 : (h.q_g > 1.0 ? 1.0 : h.q_g);
+    const double qb = h.q_b < 0.0 ? 0.0 : (h.q_b > 1.0 ? 1.0 : h.q_b);
+    PaceTile w;
+    w.n = p.n;
+    // stale fill reads every row and writes the arrived ones to g_prev
+    w.grad = row_g * (p.var.kind == kEstStaleFill ? 1.0 + qg : qg);
+    w.rep = row_r * qb;
+    w.stale = DRIFT ? row_r * (1.0 - qb) : 0.0;
+    w.in = w.out = (double)NT * kElems * 4.0 * (p.opt.kind + 1);
+    return pace_layout(st, kF32Rows, lean, per_cu, w, tiles, cus, tick_hz, q, grid, margin);
 }
 
 // The fused step's geometry follows the replica type, like the standalone
