@@ -354,9 +354,9 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * step runs at the set rate.
  *   mode         LL_PACE_AUTO (default): paced where it was measured to pay,
  *                by the number of workers and of rounds (bf16 rows: from 64
- *                workers and 3 rounds or 32 workers and 8 rounds; fp32 rows:
- *                48 and 8, 32 and 16, or 12 and 24); LL_PACE_ALWAYS;
- *                LL_PACE_NEVER.
+ *                workers and 3 rounds, 48 and 4 or 32 and 5, stale fill 32
+ *                and 3; fp32 rows: 48 and 8 and, but for stale fill, 32 and
+ *                16 or 12 and 24); LL_PACE_ALWAYS; LL_PACE_NEVER.
  *                A round takes every resident workgroup place (bf16
  *                rows) or half of them, at most 1024 tiles (fp32 rows, 4 MiB
  *                of a row per slot).
@@ -375,8 +375,7 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *                each round's lead and gap are covered by the other's
  *                streams.  Steps with fp32 replica rows always stream two
  *                (except with `persistent`), and take 0.4 of gap_us, lead_us
- *                and tail_us; bf16 steps of at least 64 workers and at most
- *                10 rounds take half of them.
+ *                and tail_us.
  *   resident     rounds sharing the workgroup places the chip holds at once
  *                (overlap..4; default 1): a round has headroom / resident of
  *                them, and rounds start no closer than a round's length /

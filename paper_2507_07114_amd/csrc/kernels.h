@@ -166,6 +166,7 @@ struct PaceParams {
 enum { kPaceAuto = 0, kPaceAlways = 1, kPaceNever = 2 };
 constexpr int64_t kPaceMaxRoundTiles = 1024;  // of fp32-row kernels
 constexpr double kPaceF32Allowance = 0.4;
+constexpr double kPaceFillCost = 1.08;  // time of a stale-fill sweep byte, in plain ones
 constexpr double kDefaultPaceRate = 6.7e12;
 constexpr double kDefaultPaceRateF32 = 6.4e12;
 constexpr double kDefaultPaceGapUs = 2.0;

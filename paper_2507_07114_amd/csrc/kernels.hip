@@ -1330,23 +1330,31 @@ int resident_per_cu(int dev, K kernel, int threads, int (&table)[kMaxDevices]) {
 
 // Whether LL_PACE_AUTO paces a step of n rows in `rounds` rounds.  Many rows
 // gain most: unpaced, the chip reads pieces of all of them at once.  Few rounds
-// lose the start and the end of the schedule, and rows of up to 64 MB (16
-// rounds of fp32 rows, 13 of bf16 ones) are served better unpaced than longer
-// ones.  Steps with drift, p = 0.1, unpaced / paced, us:
-//   fp32 rows  N = 64: 4 M 404 / 425, 8 M (8 rounds) 789 / 756, 48 M 4728 / 4103
-//              N = 32: 8 M 400 / 413, 16 M (16) 768 / 764, 25 M 1314 / 1150
-//              N = 24: 16 M 577 / 602, 33 M (32) 1322 / 1220
-//              N = 16: 16 M 387 / 439, 33 M 925 / 856;  N = 8: 33 M 521 / 525
-//   bf16 rows  N = 96: 3 M 221 / 238, 8 M 586 / 530
-//              N = 64: 3 M (2 rounds) 153 / 168, 8 M (4) 397 / 366, 13 M 703 / 655,
-//                      105 M 5520 / 4622
-//              N = 48: 13 M (6) 532 / 525, 33 M (13) 1311 / 1170
-//              N = 32: 17 M (7) 404 / 448, 33 M (13) 926 / 866
-//              N = 16: 100 M 1620 / 1645
-bool pace_pays(bool f32_rows, int n, int64_t rounds) {
+// lose the start and the end of the schedule, and few rows make rounds so short
+// that the allowances count.  Unpaced / paced, us per step with drift, p = 0.1,
+// on three sets of buffers in turn (nothing left in the caches):
+//   bf16 rows  N = 96: 4 M (2 rounds) 287 / 277, 8 M (4) 604 / 530
+//              N = 64: 3 M (2) 153 / 173, 5.2 M (3) 261 / 261, 8 M (4) 409 / 380,
+//                      13 M (6) 776 / 681, 33 M (13) 1757 / 1474, 105 M 5520 / 4622
+//              N = 48: 5.2 M (3) 200 / 211, 8 M (4) 310 / 306, 13 M (5) 520 / 471
+//              N = 32: 8 M (4) 218 / 230, 13 M (5) 369 / 350, 20 M (8) 578 / 530
+//              N = 24: 16 M (7) 351 / 362, 33 M (13) 721 / 715
+//              N = 16: 16 M 270 / 287, 100 M 1515 / 1646
+//   stale fill, bf16 rows
+//              N = 64: 8 M (4) 617 / 577, 26 M 1856 / 1783
+//              N = 32: 8 M without drift (3) 317 / 301;  N = 16: 33 M 684 / 767
+//   fp32 rows  N = 64: 4 M (4) 382 / 425, 8 M (8) 802 / 756, 50 M 4725 / 4220
+//              N = 32: 8 M (8) 412 / 413, 16 M (16) 844 / 769
+//              N = 24: 16 M (16) 598 / 605, 25 M (24) 1035 / 908
+//              N = 16: 16 M 425 / 440, 33 M (32) 932 / 856
+//              N = 12: 33 M 727 / 694;  N = 8: 33 M 530 / 531, 100 M 1485 / 1538
+//   stale fill, fp32 rows  N = 32: 16 M 1129 / 1144
+bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
     if (f32_rows)
-        return (n >= 48 && rounds >= 8) || (n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24);
-    return (n >= 64 && rounds >= 3) || (n >= 32 && rounds >= 8);
+        return (n >= 48 && rounds >= 8) ||
+               (!fill && ((n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24)));
+    return (n >= 64 && rounds >= 3) || (n >= 48 && rounds >= 4) || (n >= 32 && rounds >= 5) ||
+           (fill && n >= 32 && rounds >= 3);
 }
 }  // namespace
 
@@ -1374,6 +1382,7 @@ void set_pace_setting(const PaceSetting& st) {
 // each sweep, and of master and moments before and after the first sweep.
 struct PaceTile {
     int n;
+    bool fill;  // stale fill
     double grad, rep, stale;
     double in, out;
 };
@@ -1409,14 +1418,10 @@ static bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per
     if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
     if (gmax < 1) return false;
     const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w.n, rounds)) return false;
+    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w.fill, w.n, rounds)) return false;
     const int64_t g = (tiles + rounds - 1) / rounds;
     const double fp = 256.0 * tick_hz * k / rate;             // 1/256 ticks per byte of a round
-    // A short schedule of many rows is kept with half the allowances (N = 64
-    // bf16: 8 M 380 -> 365 us, 20 M, 8 rounds, 899 -> 866); over 13 rounds and
-    // more a late round is not made good any more (105 M, 41 rounds: 4622 us
-    // with all of them, 5480 with half).
-    const double allow = pair ? kPaceF32Allowance : (w.n >= 64 && rounds <= 10 ? 0.5 : 1.0);
+    const double allow = pair ? kPaceF32Allowance : 1.0;
     const double us = 1e-6 * tick_hz * 256.0 * allow;         // 1/256 ticks per allowed microsecond
     const double n = (double)w.n;
     const double dg = g * w.grad * fp, dr = g * w.rep * fp, ds = g * w.stale * fp;
@@ -1471,8 +1476,11 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     const double qb = h.q_b < 0.0 ? 0.0 : (h.q_b > 1.0 ? 1.0 : h.q_b);
     PaceTile w;
     w.n = p.n;
-    // stale fill reads every row and writes the arrived ones to g_prev
-    w.grad = row_g * (p.var.kind == kEstStaleFill ? 1.0 + qg : qg);
+    // Stale fill reads every row and writes the arrived ones to g_prev; this
+    // mix of reads and writes keeps 6.2e12 where the other sweeps keep 6.7e12
+    // (N = 64, 8 M: 577 us at 6.2e12, 590 at 6.4e12, 625 at 5.6e12).
+    w.fill = p.var.kind == kEstStaleFill;
+    w.grad = row_g * (w.fill ? kPaceFillCost * (1.0 + qg) : qg);
     w.rep = row_r * qb;
     w.stale = DRIFT ? row_r * (1.0 - qb) : 0.0;
     w.in = w.out = (double)NT * kElems * 4.0 * (p.opt.kind + 1);
