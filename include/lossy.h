@@ -336,7 +336,7 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
                      ll_drift* drift, const ll_ext* ext, void* stream);
 
 /*
- * Pacing of lossy_step_fused (a performance setting of this library, not part
+ * Pacing of lossy_step_fused and lossy_broadcast (a performance setting of this library, not part
  * of the paper's method; it never changes a result).  The fused step streams
  * all N gradient rows and all N replica rows of every packet.  When each
  * workgroup walks the rows on its own, the chip has pieces of every row in
@@ -405,6 +405,11 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * one-lane kernel that stores the schedule's start time in a per-device
  * device variable.  Overlapping paced steps on one device can read each
  * other's start time, which costs speed but changes no result.
+ * lossy_broadcast is paced by the same setting, as one sweep (auto: bf16 rows
+ * from 64 workers and 2 rounds, or 24 workers and workers x rounds of 160;
+ * fp32 rows from 16 workers, 8 rounds and 450), with slots for 1.045 of
+ * bytes_per_s (1.0625 of bytes_per_s_f32) and for the share of arrived rows
+ * that a small kernel, enqueued before it, samples from the masks.
  * ll_set_pacing returns LL_EINVAL for an unknown mode or a field outside the
  * ranges above (bytes_per_s and bytes_per_s_f32 in (0, 1e15), gap_us,
  * lead_us and tail_us in [0, 1e4], persistent 0 or 1 and only with overlap

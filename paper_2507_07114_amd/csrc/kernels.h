@@ -167,6 +167,10 @@ enum { kPaceAuto = 0, kPaceAlways = 1, kPaceNever = 2 };
 constexpr int64_t kPaceMaxRoundTiles = 1024;  // of fp32-row kernels
 constexpr double kPaceF32Allowance = 0.4;
 constexpr double kPaceFillCost = 1.08;  // time of a stale-fill sweep byte, in plain ones
+// A broadcast by itself, in rates of a step: 7.0e12 (N = 64, 26 M bf16: 511 us,
+// 6.7e12 531, 6.0e12 585) and 6.8e12.
+constexpr double kPaceWriteRate = 1.045;
+constexpr double kPaceWriteRateF32 = 1.0625;
 constexpr double kDefaultPaceRate = 6.7e12;
 constexpr double kDefaultPaceRateF32 = 6.4e12;
 constexpr double kDefaultPaceGapUs = 2.0;

@@ -354,9 +354,46 @@ __global__ __launch_bounds__(NT) void k_shard_step(int64_t d, OptParams o, float
     }
 }
 
-template <class R, bool W, bool SPLIT>
+// Start time of a paced sweep and the share of rows that arrive, one per
+// device, written by a small kernel before the sweep: the share is sampled from
+// the masks (2048 bytes of them; the slots it gives are within 1% or so).
+// Overlapping sweeps may read each other's, which can cost speed but never
+// changes a result.
+__device__ SweepAnchor g_sweep_anchor;
+
+__global__ __launch_bounds__(kThreads) void k_sweep_anchor(const uint8_t* arrived, int64_t total,
+                                                           uint64_t margin_ticks) {
+    constexpr int kSamples = 8;
+    __shared__ int s_count;
+    if (threadIdx.x == 0) s_count = 0;
+    __syncthreads();
+    int mine = 0;
+#pragma unroll
+    for (int u = 0; u < kSamples; ++u) {
+        // a multiplicative hash, so that no regular pattern of masks lines up
+        const uint64_t h = (uint64_t)(u * kThreads + (int)threadIdx.x) * 0x9E3779B97F4A7C15ull;
+        mine += arrived[(h >> 16) % (uint64_t)total] != 0 ? 1 : 0;
+    }
+    atomicAdd(&s_count, mine);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const uint64_t share = (uint64_t)s_count * 65536 / (kSamples * kThreads);
+    __hip_atomic_store(&g_sweep_anchor.arrived, share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&g_sweep_anchor.start, clock_ticks() + margin_ticks, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void set_pace(NoPace&, const SweepParams&, SweepAnchor*) {}
+__device__ __forceinline__ void set_pace(SweepPace& pace, const SweepParams& q, SweepAnchor* lds) {
+    pace.src = &g_sweep_anchor;
+    pace.anchor = lds;
+    pace.q = q;
+    pace.round = (uint64_t)blockIdx.x / (uint64_t)q.per_round;
+}
+
+template <class R, bool W, bool SPLIT, class Pace>
 __device__ __forceinline__ void broadcast_chunk(const BcastParams& p, const Chunk<SPLIT>& ch,
-                                                const uint64_t* words, int nw) {
+                                                const uint64_t* words, int nw, const Pace& pace) {
     Raw8<F32> th_r;
     load_chunk<W>(p.theta, ch, th_r);
     float th[8];
@@ -369,28 +406,33 @@ __device__ __forceinline__ void broadcast_chunk(const BcastParams& p, const Chun
         while (bits) {
             const int i = w * 64 + __builtin_ctzll(bits);
             bits &= bits - 1;
+            pace.row(i);
             store_row<R, W>(reps + (int64_t)i * p.ld, ch, r);
         }
     }
 }
 
-template <class R>
-__global__ __launch_bounds__(R::kPacketThreads) void k_broadcast(BcastParams p) {
+template <class R, class Pace>
+__global__ __launch_bounds__(R::kPacketThreads) void k_broadcast(BcastParams p, SweepParams q) {
     constexpr int NT = R::kPacketThreads;
     __shared__ uint64_t s_words[1][kMaxWords];
+    __shared__ SweepAnchor s_anchor;
+    Pace pace;
+    set_pace(pace, q, &s_anchor);
     const auto ch = chunk_of<R>(blockIdx.x, p.d, p.L, p.cpp);
     const MaskSource src[1] = {{false, 0, 0, p.arrived, -1, nullptr}};
     const int dirs[1] = {1};
-    stage_masks<NT, 1>(src, p.n, p.P, ch.k, 0, dirs, s_words);
+    stage_masks<NT, 1>(src, p.n, p.P, ch.k, 0, dirs, s_words, [&pace]() { pace.fetch(); });
+    pace.begin();
     if (ch.nv == 0) return;
     const int nw = (p.n + 63) >> 6;
-    if (ch.whole) broadcast_chunk<R, true>(p, ch, s_words[0], nw);
-    else broadcast_chunk<R, false>(p, ch, s_words[0], nw);
+    if (ch.whole) broadcast_chunk<R, true>(p, ch, s_words[0], nw, pace);
+    else broadcast_chunk<R, false>(p, ch, s_words[0], nw, pace);
 }
 
-template <class R, bool W, bool SPLIT>
+template <class R, bool W, bool SPLIT, class Pace>
 __device__ __forceinline__ void broadcast_flat_chunk(const BcastParams& p, const Flat<SPLIT>& f,
-                                                     const FlatLds& lds) {
+                                                     const FlatLds& lds, const Pace& pace) {
     Raw8<F32> th_r;
     load_chunk<W>(p.theta, f.ch, th_r);
     float th[8];
@@ -398,20 +440,25 @@ __device__ __forceinline__ void broadcast_flat_chunk(const BcastParams& p, const
     Raw8<R> r;
     pack(th, r);
     broadcast_flat<R, W>(reinterpret_cast<typename R::T*>(p.replicas), p.ld, f, lds.words, r,
-                         [](int) {});
+                         [&](int row) { pace.row(row); });
 }
 
-template <class R>
-__global__ __launch_bounds__(R::kPacketThreads) void k_broadcast_flat(BcastParams p) {
+template <class R, class Pace>
+__global__ __launch_bounds__(R::kPacketThreads) void k_broadcast_flat(BcastParams p,
+                                                                      SweepParams q) {
     constexpr int NT = R::kPacketThreads;
+    __shared__ SweepAnchor s_anchor;
+    Pace pace;
+    set_pace(pace, q, &s_anchor);
     const auto f = flat_at<NT, R::kSplit>(blockIdx.x, p.d, p.L, p.n, p.slots);
     const FlatLds lds(s_flat, 1, p.slots, f.nw);
     const MaskSource src[1] = {{false, 0, 0, p.arrived, -1, nullptr}};
     const int dirs[1] = {1};
-    stage_flat<NT, 1>(src, f, p.P, 0, dirs, lds.words);
+    stage_flat<NT, 1>(src, f, p.P, 0, dirs, lds.words, [&pace]() { pace.fetch(); });
+    pace.begin();
     if (f.ch.nv == 0) return;
-    if (f.ch.whole) broadcast_flat_chunk<R, true>(p, f, lds);
-    else broadcast_flat_chunk<R, false>(p, f, lds);
+    if (f.ch.whole) broadcast_flat_chunk<R, true>(p, f, lds, pace);
+    else broadcast_flat_chunk<R, false>(p, f, lds, pace);
 }
 
 // Drift of one chunk over all rows, read in ascending order.
@@ -1236,23 +1283,6 @@ hipError_t launch_shard_step(int64_t d, const OptParams& o, float* theta, float*
 }
 
 template <class R>
-static void launch_broadcast_t(BcastParams p, hipStream_t s) {
-    constexpr int NT = R::kPacketThreads;
-    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 1, 0);
-    p.cpp = t.cpp;
-    p.slots = t.slots;
-    if (t.slots)
-        hipLaunchKernelGGL(k_broadcast_flat<R>, dim3((unsigned)t.tiles), dim3(NT), t.lds, s, p);
-    else hipLaunchKernelGGL(k_broadcast<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
-}
-
-hipError_t launch_broadcast(int rdtype, const BcastParams& p, hipStream_t s) {
-    if (rdtype == 1) launch_broadcast_t<BF16>(p, s);
-    else launch_broadcast_t<F32>(p, s);
-    return hipGetLastError();
-}
-
-template <class R>
 static int64_t launch_drift_t(DriftParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 0, kFewStepRows);
@@ -1376,6 +1406,100 @@ void set_pace_setting(const PaceSetting& st) {
     g_pace_tail_us.store(st.tail_us);
     g_pace_persistent.store(st.persistent);
     g_pace_rate_f32.store(st.bytes_per_s_f32);
+}
+
+// Whether LL_PACE_AUTO paces a broadcast (masks in memory, p = 0.1, three sets
+// of buffers in turn, unpaced / paced, us):
+//   bf16 rows  N = 64: 3 M (1 round) 70 / 67, 8 M (2) 178 / 160, 26 M 615 / 511
+//              N = 32: 8 M (2) 91 / 93, 16 M (4) 173 / 178, 33 M (8) 406 / 357
+//              N = 24: 13 M (4) 106 / 125, 33 M (8) 319 / 289
+//              N = 16: 50 M (12) 335 / 329
+//   fp32 rows  N = 64: 8 M (8) 346 / 333, 25 M (24) 1108 / 950
+//              N = 48: 10 M (10) 381 / 352
+//              N = 32: 8 M (8) 175 / 180, 16 M (16) 340 / 333
+//              N = 16: 33 M (32) 407 / 366
+// An aggregate or a drift pass by itself gains nothing at any rate from 6.0 to
+// 7.0e12 (N = 64, 26 M: 624 / 622 and 672 / 690): rows read non-temporally are
+// served as well unpaced.
+bool sweep_pays(bool f32_rows, int n, int64_t rounds) {
+    if (f32_rows) return n >= 16 && rounds >= 8 && n * rounds >= 450;
+    return (n >= 64 && rounds >= 2) || (n >= 24 && n * rounds >= 160);
+}
+
+// The schedule of one sweep of writes over n rows of `row` bytes a tile, after
+// `in` bytes of vectors; false: unpaced.
+static bool sweep_plan(bool f32_rows, int per_cu, int n, double row, double in, int64_t tiles,
+                       int dev, SweepParams* q, uint64_t* margin) {
+    const PaceSetting st = get_pace_setting();
+    if (st.mode == kPaceNever || tiles <= 0 || per_cu <= 0) return false;
+    int cus = 0;
+    double tick_hz = 0.0;
+    if (!device_info(dev, &cus, &tick_hz)) return false;
+    const int k = st.overlap > 1 || f32_rows ? 2 : 1;
+    const int res = st.resident < k ? k : st.resident;
+    int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
+    if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
+    if (gmax < 1) return false;
+    const int64_t rounds = (tiles + gmax - 1) / gmax;
+    if (st.mode == kPaceAuto && !sweep_pays(f32_rows, n, rounds)) return false;
+    const int64_t g = (tiles + rounds - 1) / rounds;
+    // writes alone keep a higher rate than the step's sweeps of either kind
+    const double rate =
+        f32_rows ? kPaceWriteRateF32 * st.bytes_per_s_f32 : kPaceWriteRate * st.bytes_per_s;
+    const double fp = 256.0 * tick_hz * k / rate;
+    const double us = 1e-6 * tick_hz * 256.0 * (f32_rows ? kPaceF32Allowance : 1.0);
+    const double slot = g * row * fp;
+    const double off = st.lead_us * us + g * in * fp;
+    const double fixed = off + st.tail_us * us;
+    if (!(fixed + n * slot < 1e15)) return false;
+    q->per_round = g;
+    q->fixed = (uint64_t)fixed;
+    q->off = (uint64_t)off;
+    q->slot = (uint64_t)slot;
+    q->rows = (uint64_t)n;
+    q->share = (uint64_t)res;
+    *margin = (uint64_t)(kPaceMarginUs * 1e-6 * tick_hz) + 1;
+    q->guard = 2 * ((uint64_t)(fixed + n * slot) >> 8) + 2 * *margin + 1;
+    return true;
+}
+
+template <class R>
+static void launch_broadcast_t(BcastParams p, hipStream_t s) {
+    constexpr int NT = R::kPacketThreads;
+    constexpr double kRow = (double)NT * kElems * sizeof(typename R::T);
+    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 1, 0);
+    p.cpp = t.cpp;
+    p.slots = t.slots;
+    const dim3 grid((unsigned)t.tiles), block(NT);
+    static int occupancy[kMaxDevices], occupancy_flat[kMaxDevices];
+    SweepParams q = {};
+    uint64_t margin = 0;
+    int dev = 0;
+    bool paced = hipGetDevice(&dev) == hipSuccess;
+    if (paced) {
+        const int per_cu =
+            t.slots ? resident_per_cu(dev, k_broadcast_flat<R, SweepPace>, NT, occupancy_flat)
+                    : resident_per_cu(dev, k_broadcast<R, SweepPace>, NT, occupancy);
+        paced = sweep_plan(sizeof(typename R::T) == 4, per_cu, p.n, kRow, NT * kElems * 4.0,
+                           t.tiles, dev, &q, &margin);
+    }
+    if (paced)
+        hipLaunchKernelGGL(k_sweep_anchor, dim3(1), dim3(kThreads), 0, s, p.arrived,
+                           (int64_t)p.n * p.P, margin);
+    if (paced && t.slots)
+        hipLaunchKernelGGL((k_broadcast_flat<R, SweepPace>), grid, block, t.lds, s, p, q);
+    else if (paced)
+        hipLaunchKernelGGL((k_broadcast<R, SweepPace>), grid, block, 0, s, p, q);
+    else if (t.slots)
+        hipLaunchKernelGGL((k_broadcast_flat<R, NoPace>), grid, block, t.lds, s, p, q);
+    else
+        hipLaunchKernelGGL((k_broadcast<R, NoPace>), grid, block, 0, s, p, q);
+}
+
+hipError_t launch_broadcast(int rdtype, const BcastParams& p, hipStream_t s) {
+    if (rdtype == 1) launch_broadcast_t<BF16>(p, s);
+    else launch_broadcast_t<F32>(p, s);
+    return hipGetLastError();
 }
 
 // What one tile of a paced kernel is expected to move: bytes per row slot of

@@ -528,10 +528,27 @@ __device__ __forceinline__ void stream_rows(const typename E::T* rows, int64_t l
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t clock_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
+// Waits for clock time t, unless it is past or more than `guard` ticks away.
+__device__ __forceinline__ void wait_until(uint64_t t, uint64_t guard) {
+    uint64_t now = clock_ticks();
+    if (t <= now || t - now > guard) return;
+    // every waiting wave reads the shared clock; far from the slot it
+    // sleeps longer between reads (s_sleep n: about 64 n core clocks,
+    // 27 n ns at 2.4 GHz, so no sleep overshoots the slot)
+    while (now < t) {
+        const uint64_t rem = t - now;
+        if (rem > 100) __builtin_amdgcn_s_sleep(16);
+        else if (rem > 20) __builtin_amdgcn_s_sleep(4);
+        else __builtin_amdgcn_s_sleep(1);
+        now = clock_ticks();
+    }
+}
+
 // Accessors without pacing (one-stage kernels and the unpaced fused step).
 struct NoPace {
     __device__ __forceinline__ void fetch() const {}
     __device__ __forceinline__ void begin() {}
+    __device__ __forceinline__ void row(int) const {}
     __device__ __forceinline__ void grad(int) const {}
     __device__ __forceinline__ void rep(int) const {}
     __device__ __forceinline__ void stale(int) const {}
@@ -578,23 +595,51 @@ struct ClockPace {
     // overlaps them.
     __device__ __forceinline__ void begin() { base = *anchor + round_start; }
     __device__ __forceinline__ void at(uint64_t off, uint64_t delta, int i) const {
-        const uint64_t t = base + ((off + (uint64_t)i * delta) >> 8);
-        uint64_t now = clock_ticks();
-        if (t <= now || t - now > guard) return;
-        // every waiting wave reads the shared clock; far from the slot it
-        // sleeps longer between reads (s_sleep n: about 64 n core clocks,
-        // 27 n ns at 2.4 GHz, so no sleep overshoots the slot)
-        while (now < t) {
-            const uint64_t rem = t - now;
-            if (rem > 100) __builtin_amdgcn_s_sleep(16);
-            else if (rem > 20) __builtin_amdgcn_s_sleep(4);
-            else __builtin_amdgcn_s_sleep(1);
-            now = clock_ticks();
-        }
+        wait_until(base + ((off + (uint64_t)i * delta) >> 8), guard);
     }
     __device__ __forceinline__ void grad(int i) const { at(off_g, dg, i); }
     __device__ __forceinline__ void rep(int i) const { at(off_r, dr, i); }
     __device__ __forceinline__ void stale(int i) const { at(off_s, ds, i); }
+};
+
+// Pace of a kernel with a single sweep (the broadcast) whose share of arrived rows the host
+// does not know: the anchor kernel samples it from the masks and stores it
+// beside the start time, in 1/65536, and the slots and rounds scale with it.
+struct SweepParams {
+    int64_t per_round;
+    uint64_t fixed;        // of a round besides its slots, 1/256 ticks
+    uint64_t off;          // first slot after the round's start, 1/256 ticks
+    uint64_t slot;         // slot length if every row arrived, 1/256 ticks
+    uint64_t rows, share;  // rows; rounds that share the places
+    uint64_t guard;        // ticks
+};
+
+struct SweepAnchor {
+    uint64_t start, arrived;
+};
+
+struct SweepPace {
+    const SweepAnchor* src;
+    SweepAnchor* anchor;  // LDS
+    SweepParams q;
+    uint64_t round, base, delta;
+    __device__ __forceinline__ void fetch() const {
+        if (threadIdx.x == 0) {
+            anchor->start =
+                __hip_atomic_load(&src->start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            anchor->arrived =
+                __hip_atomic_load(&src->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // after a barrier that follows fetch()
+    __device__ __forceinline__ void begin() {
+        delta = uniform64((q.slot * anchor->arrived) >> 16);
+        const uint64_t length = (q.fixed + q.rows * delta) / q.share;
+        base = uniform64(anchor->start) + ((round * length + q.off) >> 8);
+    }
+    __device__ __forceinline__ void row(int i) const {
+        wait_until(base + (((uint64_t)i * delta) >> 8), q.guard);
+    }
 };
 
 // ---------------------------------------------------------------------------
