@@ -155,9 +155,9 @@ struct PaceParams {
 // Pacing modes and defaults: the schedule is laid out for kDefaultPaceRate
 // bytes/s (kDefaultPaceRateF32 for steps with fp32 replica rows) with
 // kDefaultPaceGapUs between the gradient and replica sweeps, and starts
-// kPaceMarginUs after the anchor is written.  The rates, on three cards (rows
-// loaded non-temporally; N = 64, kept in every one of 20 to 80 steps in a row
-// unless marked):
+// kPaceMarginUs after the anchor is written.  The rates (rows loaded
+// non-temporally; N = 64, means of 20 to 80 steps in a row, the same to 0.2%
+// in every run unless marked):
 //   bf16 rows, 105 M  6.3e12 4888 us, 6.6e12 4685, 6.7e12 4622, 6.8e12 4560,
 //                     6.9e12 4580-4720 (slips), 7.0e12 5300 (never kept)
 //   fp32 rows, 48 M   one round streaming: 5.9e12 4696, 6.5e12 4336, 6.7e12
