@@ -895,6 +895,21 @@ struct Drift8 {
             }
         }
     }
+    // The same for the elements of mask `elems`; the others hold the reference
+    // and add nothing, whatever the reference is and x has there.
+    __device__ __forceinline__ void add_some(const float (&x)[8], const float (&r)[8],
+                                             uint32_t elems) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t on = 0u - ((elems >> j) & 1u);
+            const uint32_t xb = __float_as_uint(x[j]) & on, rb = __float_as_uint(r[j]);
+            const double d = (double)__uint_as_float(xb) - (double)__uint_as_float(rb & on);
+            s1[j] = s1[j] + d;
+            s2[j] = __fma_rn(d, d, s2[j]);
+            abs_sum = abs_sum + fabs(d);
+            b.add(j, __uint_as_float(xb | (rb & ~on)));
+        }
+    }
     // Fold into per-thread totals: pair sum N*S2 - S1^2 per element (clamped
     // at 0 against rounding, so that identical rows give exactly 0) and the
     // max range.

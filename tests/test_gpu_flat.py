@@ -170,3 +170,41 @@ def test_flat_aggregate_stage(est, gdtype):
     # a sequential fp32 sum of n terms of either sign and two more roundings
     tol = 1e-5 * x.abs().sum(0).clamp(min=1.0)
     assert ((g_hat.double() - want).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("gdtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("p", [0.5, 1.0])
+def test_flat_drift_skips_nonfinite_elements_that_arrived(gdtype, p):
+    """A master value that is infinite, NaN or overflows the replica type adds
+    nothing to the drift where every row holds it, also beside an element of a
+    lossy packet in the same vector: such a row's drift is that of the other
+    elements."""
+    n, d, L = 5, 10_003, 333  # whole tiles and a ragged end
+    P = -(-d // L)
+    print(f"flat nonfinite {gdtype} p={p}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    sure = torch.zeros(P, dtype=torch.uint8, device=DEV)
+    sure[::2] = 1
+    on_sure = sure.bool().repeat_interleave(L)[:d]
+    ld = -(-d // 8) * 8
+    theta = torch.randn(d, generator=gen, device=DEV)
+    replicas = torch.zeros((n, ld), dtype=gdtype, device=DEV)
+    replicas[:, :d] = (theta + 0.1 * torch.randn((n, d), generator=gen, device=DEV)).to(gdtype)
+    at = torch.arange(d, device=DEV) % L
+    edge = on_sure & ((at < 4) | (at >= L - 4))
+    odd = torch.tensor([float("inf"), float("-inf"), float("nan"), 3.4e38], device=DEV)
+    theta[edge] = odd[torch.arange(int(edge.sum()), device=DEV) % 4]
+    drift = ll.drift_buffer()
+    ws = torch.zeros(ll.ll_workspace_bytes(n, d, L), dtype=torch.uint8, device=DEV)
+    loss = ll.bernoulli(p, seed=5)
+    ll.lossy_step_fused(d=d, packet=L, step=0, loss_g=loss, loss_b=loss,
+                        grads=torch.zeros((n, ld), dtype=gdtype, device=DEV), opt=ll.sgd(0.0),
+                        theta=theta, replicas=replicas, workspace=ws, drift=drift,
+                        ext=ll.ext(reliable=sure))
+    got = ll.read_drift(drift)
+    rest, ref = replicas.clone(), theta.clone()
+    rest[:, :d][:, on_sure] = 0
+    ref[on_sure] = 0
+    want = parity.torch_drift(rest, ref, d)
+    assert want["mean_abs_to_master"] > 0
+    parity.check_drift_close(got, want, f"{gdtype} p={p}")
