@@ -36,6 +36,7 @@ PMC_PROFILE = os.path.join(HERE, "profiles", "k_step_paced_n64_llama7b_shard_pmc
 KERNEL_SOURCES = ["paper_2507_07114_amd/csrc/kernels.hip",
                   "paper_2507_07114_amd/csrc/lossy_device.h",
                   "paper_2507_07114_amd/csrc/flat_tile.h",
+                  "paper_2507_07114_amd/csrc/dispatch.h",
                   "paper_2507_07114_amd/csrc/kernels.h"]
 
 

@@ -17,20 +17,9 @@ namespace lossy {
 // mask of its own packet.  A thread's group of elements may straddle two
 // packets: each lane carries an 8-bit element mask per row.
 // ---------------------------------------------------------------------------
-constexpr int kFlatMinPacket = 64;                // a group touches at most two packets
-constexpr int64_t kFlatMaxPacket = 1ll << 30;     // 32-bit offsets within a packet
 // Byte offset past the end of every buffer resource of a tile: a load there
 // gives zeros and a store is dropped, with no memory access.
 constexpr int kBufferPast = 1 << 30;
-
-// Most packets that a run of `tile` elements can touch.
-__host__ __device__ constexpr int flat_slots(int tile, int64_t L) {
-    return (int)((tile - 2) / L) + 2;
-}
-
-__host__ __device__ constexpr size_t flat_lds_bytes(int ndir, int slots, int n) {
-    return (size_t)slots * ((size_t)ndir * ((n + 63) / 64) * 8 + 8);
-}
 
 template <bool SPLIT>
 struct Flat {

@@ -142,60 +142,6 @@ struct FusedParams {
     uint8_t* pre[2];
 };
 
-// Slot schedule of the paced fused step (see ClockPace), times in 1/256
-// clock ticks relative to each round's start.
-struct PaceParams {
-    int64_t per_round;             // workgroups (tiles) per round
-    uint64_t round;                // time between round starts
-    uint64_t off_g, off_r, off_s;  // gradient, replica and stale-read sweep starts
-    uint64_t dg, dr, ds;           // slot lengths of the three sweeps
-    uint64_t guard;                // longest wait, ticks
-};
-
-// Pacing modes and defaults: the schedule is laid out for kDefaultPaceRate
-// bytes/s (kDefaultPaceRateF32 for steps with fp32 replica rows) with
-// kDefaultPaceGapUs between the gradient and replica sweeps, and starts
-// kPaceMarginUs after the anchor is written.  The rates (rows loaded
-// non-temporally; N = 64, means of 20 to 80 steps in a row, the same to 0.2%
-// in every run unless marked):
-//   bf16 rows, 105 M  6.3e12 4888 us, 6.6e12 4685, 6.7e12 4622, 6.8e12 4560,
-//                     6.9e12 4580-4720 (slips), 7.0e12 5300 (never kept)
-//   fp32 rows, 48 M   one round streaming: 5.9e12 4696, 6.5e12 4336, 6.7e12
-//                     4380 (slips); two: 6.2e12 4497, 6.4e12 4103 with 0.4 of
-//                     the allowances, 6.6e12 3983 (25 M: slips)
-enum { kPaceAuto = 0, kPaceAlways = 1, kPaceNever = 2 };
-constexpr int64_t kPaceMaxRoundTiles = 1024;  // of fp32-row kernels
-constexpr double kPaceF32Allowance = 0.4;
-constexpr double kPaceFillCost = 1.08;  // time of a stale-fill sweep byte, in plain ones
-// A broadcast by itself, in rates of a step: 7.0e12 (N = 64, 26 M bf16: 511 us,
-// 6.7e12 531, 6.0e12 585) and 6.8e12.
-constexpr double kPaceWriteRate = 1.045;
-constexpr double kPaceWriteRateF32 = 1.0625;
-constexpr double kDefaultPaceRate = 6.7e12;
-constexpr double kDefaultPaceRateF32 = 6.4e12;
-constexpr double kDefaultPaceGapUs = 2.0;
-constexpr double kDefaultPaceLeadUs = 4.0;
-constexpr int kDefaultPaceOverlap = 1;
-constexpr int kDefaultPaceResident = 1;
-constexpr double kPaceMarginUs = 3.0;
-constexpr double kDefaultPaceTailUs = 3.0;
-constexpr int kDefaultPacePersistent = 0;
-// Fraction of the resident workgroup places the rounds in flight may fill.
-constexpr double kDefaultPaceHeadroom = 1.0;
-
-// How the fused step is paced (process-wide; see ll_set_pacing).
-struct PaceSetting {
-    int mode;            // 0 auto, 1 always, 2 never
-    double bytes_per_s;  // rate the schedule is laid out for
-    double gap_us;       // allowance between the last gradient row and the first replica row
-    double lead_us;      // allowance from a round's start to its first gradient row
-    int overlap;         // rounds streaming at once (1 or 2)
-    int resident;        // rounds the resident workgroup places are shared by (>= overlap)
-    double headroom;     // fraction of the resident places the rounds may fill
-    double tail_us;      // allowance after a round's last slot
-    int persistent;      // 1: one round of workgroups loops over the rounds (plain steps)
-    double bytes_per_s_f32;  // rate for steps whose replica rows are fp32
-};
 PaceSetting get_pace_setting();
 void set_pace_setting(const PaceSetting& s);
 

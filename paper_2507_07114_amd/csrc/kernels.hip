@@ -1214,57 +1214,14 @@ hipError_t launch_masks_ge(const GeLaunch& L, int ndir, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tiles of a kernel over rows of type E: chunks of one packet each (cpp per
-// packet, slots = 0), or flat tiles (slots > 0) where a packet's chunks would
-// start off the 128-byte lines or leave much of a workgroup idle.  A chunk
-// tile's masks are wave-uniform, so it is the better one where it is full.
-// Measured, chunk tiles against flat ones (us per step, Adam with drift, p =
-// 0.1, d and N as given):
-//   off the lines (L not a multiple of 64 elements)
-//     bf16 N = 64, 16 M  L = 750: 3383 / 882   6000: 879 / 786   8184: 892 / 786
-//     bf16 N = 8, 8 M    L = 750: 419 / 97     6000: 85 / 91     20000: 84 / 91
-//     broadcast, bf16 N = 32, 8 M              6000: 114 / 92    8184: 122 / 92
-//   on the lines, by the share of the threads that a packet's chunks fill
-//     bf16 N = 64, 16 M  12%: 5960 / 916  75%: 1021 / 798  87%: 767 / 841 (L =
-//                        1792), 799 / 788 (3584)  94%: 775 / -
-//     bf16 N = 8, 8 M    12%: 279 / 103   75%: 89 / 92     87%: 86 / 93
-//     fp32 N = 64, 8 M   25%: 3102 / 827  87%: 895 / 797   94%: 842 / 800
-//     fp32 N = 16, 4 M   25%: 139 / 115   87%: 114 / 115
-//     bf16 83% (L = 5120)  N = 8, 8 M: 85 / 92   N = 32: 211 / 216   N = 64, 16 M:
-//                        913 / 784
-// The share lies at 95% for fp32 rows and at 85% for bf16 rows, 80% below 48
-// of them.  A multiple of 8 off the lines stays with chunk tiles below `few`
-// rows: 12 in a step (and in the drift pass, whose partials are the step's),
-// where little of the time is row traffic, and none in an aggregate or a
-// broadcast by itself.  And a multiple of 8 stays with chunk tiles as long as
-// they are so few that most run at once: then the time is one tile's, and a
-// flat tile's code is the longer one (N = 64 bf16, L = 256: 0.2 M 30 / 49 with
-// 782 chunk tiles, 0.8 M 85 / 63 with 3125; N = 16: 20 / 23 and 46 / 27; fp32
-// N = 64, whose workgroups are half as large: 31 / 53 and 92 / 97).
-constexpr int kFewStepRows = 12;
-struct TileGrid {
-    int64_t tiles;
-    int cpp, slots;
-    size_t lds;  // dynamic LDS of a flat tile
-};
-template <class E>
-static TileGrid tile_grid(int n, int64_t d, int64_t P, int64_t L, int ndir, int few) {
-    constexpr int T = E::kPacketThreads * kElems;
-    const int percent = sizeof(typename E::T) == 4 ? 95 : (n >= 48 ? 85 : 80);
-    const int64_t cpp = (L + T - 1) / T;
-    const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
-    const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
-    const bool small = L % 8 == 0 && P * cpp <= (sizeof(typename E::T) == 4 ? 4096 : 1024);
-    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small)
-        return TileGrid{P * cpp, (int)cpp, 0, 0};
-    const int slots = flat_slots(T, L);
-    return TileGrid{(d + T - 1) / T, 0, slots, flat_lds_bytes(ndir, slots, n)};
-}
+static_assert(F32::kPacketThreads * kElems == tile_elems(true) &&
+                  BF16::kPacketThreads * kElems == tile_elems(false),
+              "tiles of the launches and of the kernels");
 
 template <class G>
 static void launch_aggregate_t(AggParams p, hipStream_t s) {
     constexpr int NT = G::kPacketThreads;
-    const TileGrid t = tile_grid<G>(p.n, p.d, p.P, p.L, 1, 0);
+    const TileGrid t = tile_grid(sizeof(typename G::T) == 4, p.n, p.d, p.P, p.L, 1, 0);
     p.cpp = t.cpp;
     p.slots = t.slots;
     if (t.slots)
@@ -1302,7 +1259,7 @@ hipError_t launch_shard_step(int64_t d, const OptParams& o, float* theta, float*
 template <class R>
 static int64_t launch_drift_t(DriftParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
-    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 0, kFewStepRows);
+    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, p.n, p.d, p.P, p.L, 0, kFewStepRows);
     p.cpp = t.cpp;
     p.slots = t.slots;
     if (t.slots) hipLaunchKernelGGL(k_drift_flat<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
@@ -1375,34 +1332,6 @@ int resident_per_cu(int dev, K kernel, int threads, int (&table)[kMaxDevices]) {
     return table[dev] > 0 ? table[dev] : 0;
 }
 
-// Whether LL_PACE_AUTO paces a step of n rows in `rounds` rounds.  Many rows
-// gain most: unpaced, the chip reads pieces of all of them at once.  Few rounds
-// lose the start and the end of the schedule, and few rows make rounds so short
-// that the allowances count.  Unpaced / paced, us per step with drift, p = 0.1,
-// on three sets of buffers in turn (nothing left in the caches):
-//   bf16 rows  N = 96: 4 M (2 rounds) 287 / 277, 8 M (4) 604 / 530
-//              N = 64: 3 M (2) 153 / 173, 5.2 M (3) 261 / 261, 8 M (4) 409 / 380,
-//                      13 M (6) 776 / 681, 33 M (13) 1757 / 1474, 105 M 5520 / 4622
-//              N = 48: 5.2 M (3) 200 / 211, 8 M (4) 310 / 306, 13 M (5) 520 / 471
-//              N = 32: 8 M (4) 218 / 230, 13 M (5) 369 / 350, 20 M (8) 578 / 530
-//              N = 24: 16 M (7) 351 / 362, 33 M (13) 721 / 715
-//              N = 16: 16 M 270 / 287, 100 M 1515 / 1646
-//   stale fill, bf16 rows
-//              N = 64: 8 M (4) 617 / 577, 26 M 1856 / 1783
-//              N = 32: 8 M without drift (3) 317 / 301;  N = 16: 33 M 684 / 767
-//   fp32 rows  N = 64: 4 M (4) 382 / 425, 8 M (8) 802 / 756, 50 M 4725 / 4220
-//              N = 32: 8 M (8) 412 / 413, 16 M (16) 844 / 769
-//              N = 24: 16 M (16) 598 / 605, 25 M (24) 1035 / 908
-//              N = 16: 16 M 425 / 440, 33 M (32) 932 / 856
-//              N = 12: 33 M 727 / 694;  N = 8: 33 M 530 / 531, 100 M 1485 / 1538
-//   stale fill, fp32 rows  N = 32: 16 M 1129 / 1144
-bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
-    if (f32_rows)
-        return (n >= 48 && rounds >= 8) ||
-               (!fill && ((n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24)));
-    return (n >= 64 && rounds >= 3) || (n >= 48 && rounds >= 4) || (n >= 32 && rounds >= 5) ||
-           (fill && n >= 32 && rounds >= 3);
-}
 }  // namespace
 
 PaceSetting get_pace_setting() {
@@ -1425,66 +1354,11 @@ void set_pace_setting(const PaceSetting& st) {
     g_pace_rate_f32.store(st.bytes_per_s_f32);
 }
 
-// Whether LL_PACE_AUTO paces a broadcast (masks in memory, p = 0.1, three sets
-// of buffers in turn, unpaced / paced, us):
-//   bf16 rows  N = 64: 3 M (1 round) 70 / 67, 8 M (2) 178 / 160, 26 M 615 / 511
-//              N = 32: 8 M (2) 91 / 93, 16 M (4) 173 / 178, 33 M (8) 406 / 357
-//              N = 24: 13 M (4) 106 / 125, 33 M (8) 319 / 289
-//              N = 16: 50 M (12) 335 / 329
-//   fp32 rows  N = 64: 8 M (8) 346 / 333, 25 M (24) 1108 / 950
-//              N = 48: 10 M (10) 381 / 352
-//              N = 32: 8 M (8) 175 / 180, 16 M (16) 340 / 333
-//              N = 16: 33 M (32) 407 / 366
-// An aggregate or a drift pass by itself gains nothing at any rate from 6.0 to
-// 7.0e12 (N = 64, 26 M: 624 / 622 and 672 / 690): rows read non-temporally are
-// served as well unpaced.
-bool sweep_pays(bool f32_rows, int n, int64_t rounds) {
-    if (f32_rows) return n >= 16 && rounds >= 8 && n * rounds >= 450;
-    return (n >= 64 && rounds >= 2) || (n >= 24 && n * rounds >= 160);
-}
-
-// The schedule of one sweep of writes over n rows of `row` bytes a tile, after
-// `in` bytes of vectors; false: unpaced.
-static bool sweep_plan(bool f32_rows, int per_cu, int n, double row, double in, int64_t tiles,
-                       int dev, SweepParams* q, uint64_t* margin) {
-    const PaceSetting st = get_pace_setting();
-    if (st.mode == kPaceNever || tiles <= 0 || per_cu <= 0) return false;
-    int cus = 0;
-    double tick_hz = 0.0;
-    if (!device_info(dev, &cus, &tick_hz)) return false;
-    const int k = st.overlap > 1 || f32_rows ? 2 : 1;
-    const int res = st.resident < k ? k : st.resident;
-    int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
-    if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
-    if (gmax < 1) return false;
-    const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !sweep_pays(f32_rows, n, rounds)) return false;
-    const int64_t g = (tiles + rounds - 1) / rounds;
-    // writes alone keep a higher rate than the step's sweeps of either kind
-    const double rate =
-        f32_rows ? kPaceWriteRateF32 * st.bytes_per_s_f32 : kPaceWriteRate * st.bytes_per_s;
-    const double fp = 256.0 * tick_hz * k / rate;
-    const double us = 1e-6 * tick_hz * 256.0 * (f32_rows ? kPaceF32Allowance : 1.0);
-    const double slot = g * row * fp;
-    const double off = st.lead_us * us + g * in * fp;
-    const double fixed = off + st.tail_us * us;
-    if (!(fixed + n * slot < 1e15)) return false;
-    q->per_round = g;
-    q->fixed = (uint64_t)fixed;
-    q->off = (uint64_t)off;
-    q->slot = (uint64_t)slot;
-    q->rows = (uint64_t)n;
-    q->share = (uint64_t)res;
-    *margin = (uint64_t)(kPaceMarginUs * 1e-6 * tick_hz) + 1;
-    q->guard = 2 * ((uint64_t)(fixed + n * slot) >> 8) + 2 * *margin + 1;
-    return true;
-}
-
 template <class R>
 static void launch_broadcast_t(BcastParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     constexpr double kRow = (double)NT * kElems * sizeof(typename R::T);
-    const TileGrid t = tile_grid<R>(p.n, p.d, p.P, p.L, 1, 0);
+    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, p.n, p.d, p.P, p.L, 1, 0);
     p.cpp = t.cpp;
     p.slots = t.slots;
     const dim3 grid((unsigned)t.tiles), block(NT);
@@ -1497,8 +1371,12 @@ static void launch_broadcast_t(BcastParams p, hipStream_t s) {
         const int per_cu =
             t.slots ? resident_per_cu(dev, k_broadcast_flat<R, SweepPace>, NT, occupancy_flat)
                     : resident_per_cu(dev, k_broadcast<R, SweepPace>, NT, occupancy);
-        paced = sweep_plan(sizeof(typename R::T) == 4, per_cu, p.n, kRow, NT * kElems * 4.0,
-                           t.tiles, dev, &q, &margin);
+        const PaceSetting st = get_pace_setting();
+        int cus = 0;
+        double tick_hz = 0.0;
+        paced = st.mode != kPaceNever && per_cu > 0 && device_info(dev, &cus, &tick_hz) &&
+                sweep_layout(st, sizeof(typename R::T) == 4, per_cu, p.n, kRow, NT * kElems * 4.0,
+                             t.tiles, cus, tick_hz, &q, &margin);
     }
     if (paced)
         hipLaunchKernelGGL(k_sweep_anchor, dim3(1), dim3(kThreads), 0, s, p.arrived,
@@ -1517,82 +1395,6 @@ hipError_t launch_broadcast(int rdtype, const BcastParams& p, hipStream_t s) {
     if (rdtype == 1) launch_broadcast_t<BF16>(p, s);
     else launch_broadcast_t<F32>(p, s);
     return hipGetLastError();
-}
-
-// What one tile of a paced kernel is expected to move: bytes per row slot of
-// each sweep, and of master and moments before and after the first sweep.
-struct PaceTile {
-    int n;
-    bool fill;  // stale fill
-    double grad, rep, stale;
-    double in, out;
-};
-
-// Lay out the schedule of a paced kernel with `tiles` tiles, `per_cu`
-// workgroups of it resident per compute unit, or return false to run it
-// unpaced.  `overlap` rounds stream at once, each covering *grid
-// adjacent tiles (`resident` rounds fill at most kPaceHeadroom of the
-// resident workgroup places; rounds are balanced) and laid out for its
-// share, rate / overlap, of the bandwidth.  A round is: a
-// lead for the workgroups to start, draw masks and read their master and
-// moments; the gradient sweep; the gap for the update and the master and
-// moment writes; the replica sweep; the stale-read sweep.  Each sweep's slot
-// lasts as long as the rows that slot is expected to move take at the
-// round's share.  Rounds start round / overlap apart, so with two in flight
-// one round's gradient sweep runs beside the previous round's replica sweep
-// and each round's lead, gap and tail are covered by the other's streams.
-static bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per_cu,
-                        const PaceTile& w, int64_t tiles, int cus, double tick_hz, PaceParams* q,
-                        int64_t* grid, uint64_t* margin) {
-    // Rounds of fp32-row kernels hold half of the 2048 places (one row slot
-    // streams 4 MiB; rounds of all places were measured slower), so the
-    // other half takes the next round while one streams: two rounds stream at
-    // once, and since each covers the other's lead, gap and tail, 0.4 of
-    // those is enough.  Rounds of bf16-row kernels take every place (1280
-    // with drift, 1536 without): two rounds at once fall behind their
-    // schedule there.
-    const bool pair = f32_rows && !lean;
-    const double rate = f32_rows ? st.bytes_per_s_f32 : st.bytes_per_s;
-    const int k = st.overlap > 1 || pair ? 2 : 1;
-    const int res = st.resident < k ? k : st.resident;
-    int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
-    if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
-    if (gmax < 1) return false;
-    const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w.fill, w.n, rounds)) return false;
-    const int64_t g = (tiles + rounds - 1) / rounds;
-    const double fp = 256.0 * tick_hz * k / rate;             // 1/256 ticks per byte of a round
-    const double allow = pair ? kPaceF32Allowance : 1.0;
-    const double us = 1e-6 * tick_hz * 256.0 * allow;         // 1/256 ticks per allowed microsecond
-    const double n = (double)w.n;
-    const double dg = g * w.grad * fp, dr = g * w.rep * fp, ds = g * w.stale * fp;
-    const double off_g = st.lead_us * us + g * w.in * fp;
-    const double off_r = off_g + n * dg + g * w.out * fp + st.gap_us * us;
-    const double off_s = off_r + n * dr;
-    // A round's workgroups leave a little after its last slot: the last rows
-    // they read must arrive and the drift partial be folded.
-    const double length = off_s + n * ds + st.tail_us * us;
-    // Rounds start `spacing` apart: no closer than the round's bytes at its
-    // share allow with k rounds streaming (stream / k), and far enough apart
-    // that a round's workgroups find places when it starts, res rounds
-    // sharing the resident places (length / res).  With k = 2 and res = 3
-    // the lead, gap and tail of each round are covered by the other rounds'
-    // streams.
-    const double stream = n * (dg + dr + ds) + g * (w.in + w.out) * fp;
-    const double spacing = stream / k > length / res ? stream / k : length / res;
-    if (!(length < 1e15)) return false;
-    q->per_round = g;
-    q->dg = (uint64_t)dg;
-    q->dr = (uint64_t)dr;
-    q->ds = (uint64_t)ds;
-    q->off_g = (uint64_t)off_g;
-    q->off_r = (uint64_t)off_r;
-    q->off_s = (uint64_t)off_s;
-    q->round = (uint64_t)spacing;
-    *margin = (uint64_t)(kPaceMarginUs * 1e-6 * tick_hz) + 1;
-    q->guard = 2 * ((uint64_t)length >> 8) + 2 * *margin + 1;
-    *grid = g;
-    return true;
 }
 
 // The schedule of a fused step.
@@ -1634,7 +1436,7 @@ template <class G, class R, bool DRIFT>
 static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     FusedParams pp = p;
-    const TileGrid t = tile_grid<R>(pp.n, pp.d, pp.P, pp.L, 2, kFewStepRows);
+    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, pp.n, pp.d, pp.P, pp.L, 2, kFewStepRows);
     const int64_t tiles = t.tiles;
     pp.cpp = t.cpp;
     pp.slots = t.slots;

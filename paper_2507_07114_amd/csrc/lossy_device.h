@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.h"
+
 namespace lossy {
 
 constexpr int kThreads = 256;  // threads per workgroup of the flat kernels (4 waves)
@@ -605,15 +607,6 @@ struct ClockPace {
 // Pace of a kernel with a single sweep (the broadcast) whose share of arrived rows the host
 // does not know: the anchor kernel samples it from the masks and stores it
 // beside the start time, in 1/65536, and the slots and rounds scale with it.
-struct SweepParams {
-    int64_t per_round;
-    uint64_t fixed;        // of a round besides its slots, 1/256 ticks
-    uint64_t off;          // first slot after the round's start, 1/256 ticks
-    uint64_t slot;         // slot length if every row arrived, 1/256 ticks
-    uint64_t rows, share;  // rows; rounds that share the places
-    uint64_t guard;        // ticks
-};
-
 struct SweepAnchor {
     uint64_t start, arrived;
 };
