@@ -170,8 +170,9 @@ inline bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
            (fill && n >= 32 && rounds >= 3);
 }
 
-// Whether LL_PACE_AUTO paces a broadcast (masks in memory, p = 0.1, three sets
-// of buffers in turn, unpaced / paced, us):
+// Whether LL_PACE_AUTO paces a broadcast of `tiles` tiles in rounds of at most
+// `places` (masks in memory, p = 0.1, three sets of buffers in turn, unpaced /
+// paced, us):
 //   bf16 rows  N = 64: 3 M (1 round) 70 / 67, 8 M (2) 178 / 160, 26 M 615 / 511
 //              N = 32: 8 M (2) 91 / 93, 16 M (4) 173 / 178, 33 M (8) 406 / 357
 //              N = 24: 13 M (4) 106 / 125, 33 M (8) 319 / 289
@@ -180,26 +181,39 @@ inline bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
 //              N = 48: 10 M (10) 381 / 352
 //              N = 32: 8 M (8) 175 / 180, 16 M (16) 340 / 333
 //              N = 16: 33 M (32) 407 / 366
+// One round of very many bf16 rows gains if a row's slot is longer than the
+// wait for it (about 0.1 us, 0.23 us on flat tiles) and all of them outweigh
+// the anchor launch and the lead, 12 us:
+//   chunks     N = 160: 1 tile 17 / 29, 500 tiles 58 / 59, 818 95 / 86
+//              N = 400: 200 57 / 59, 327 96 / 88;  N = 800: 100 57 / 88, 163 92 / 89
+//              N = 1024: 127 86 / 108, 195 138 / 123
+//   flat       N = 160: 500 75 / 65;  N = 400: 200 81 / 106, 275 123 / 120
+//              N = 800: 200 152 / 192, 325 274 / 269;  N = 1024: 253 241 / 244
 // An aggregate or a drift pass by itself gains nothing at any rate from 6.0 to
 // 7.0e12 (N = 64, 26 M: 624 / 622 and 672 / 690): rows read non-temporally are
 // served as well unpaced.
-inline bool sweep_pays(bool f32_rows, int n, int64_t rounds) {
+constexpr int kSweepOneRoundRows = 160;
+inline bool sweep_pays(bool f32_rows, bool flat, int n, int64_t tiles, int64_t places) {
+    const int64_t rounds = (tiles + places - 1) / places;
     if (f32_rows) return n >= 16 && rounds >= 8 && n * rounds >= 450;
-    return (n >= 64 && rounds >= 2) || (n >= 24 && n * rounds >= 160);
+    if (rounds < 2)
+        return n >= kSweepOneRoundRows &&
+               (flat ? tiles >= 272 : tiles >= 160 && n * tiles >= 131072);
+    return n >= 64 || (n >= 24 && n * rounds >= 160);
 }
 
 // The schedule of one sweep of writes over n rows of `row` bytes a tile, after
 // `in` bytes of vectors; false: unpaced.
-inline bool sweep_layout(const PaceSetting& st, bool f32_rows, int per_cu, int n, double row,
-                         double in, int64_t tiles, int cus, double tick_hz, SweepParams* q,
-                         uint64_t* margin) {
+inline bool sweep_layout(const PaceSetting& st, bool f32_rows, bool flat, int per_cu, int n,
+                         double row, double in, int64_t tiles, int cus, double tick_hz,
+                         SweepParams* q, uint64_t* margin) {
     const int k = st.overlap > 1 || f32_rows ? 2 : 1;
     const int res = st.resident < k ? k : st.resident;
     int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
     if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
     if (gmax < 1) return false;
     const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !sweep_pays(f32_rows, n, rounds)) return false;
+    if (st.mode == kPaceAuto && !sweep_pays(f32_rows, flat, n, tiles, gmax)) return false;
     const int64_t g = (tiles + rounds - 1) / rounds;
     // writes alone keep a higher rate than the step's sweeps of either kind
     const double rate =

@@ -1375,8 +1375,8 @@ static void launch_broadcast_t(BcastParams p, hipStream_t s) {
         int cus = 0;
         double tick_hz = 0.0;
         paced = st.mode != kPaceNever && per_cu > 0 && device_info(dev, &cus, &tick_hz) &&
-                sweep_layout(st, sizeof(typename R::T) == 4, per_cu, p.n, kRow, NT * kElems * 4.0,
-                             t.tiles, cus, tick_hz, &q, &margin);
+                sweep_layout(st, sizeof(typename R::T) == 4, t.slots > 0, per_cu, p.n, kRow,
+                             NT * kElems * 4.0, t.tiles, cus, tick_hz, &q, &margin);
     }
     if (paced)
         hipLaunchKernelGGL(k_sweep_anchor, dim3(1), dim3(kThreads), 0, s, p.arrived,

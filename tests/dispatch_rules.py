@@ -42,11 +42,12 @@ int step_layout(const double* st, int f32, int lean, int per_cu, int n, int fill
     for (int i = 0; i < 8; ++i) out[i] = v[i];
     return 1;
 }
-int write_layout(const double* st, int f32, int per_cu, int n, double row, double in,
+int write_layout(const double* st, int f32, int flat, int per_cu, int n, double row, double in,
                  int64_t tiles, int cus, double hz, double* out) {
     SweepParams q;
     uint64_t margin;
-    if (!sweep_layout(setting(st), f32, per_cu, n, row, in, tiles, cus, hz, &q, &margin)) return 0;
+    if (!sweep_layout(setting(st), f32, flat, per_cu, n, row, in, tiles, cus, hz, &q, &margin))
+        return 0;
     const double v[] = {(double)q.per_round, (double)q.fixed, (double)q.off, (double)q.slot};
     for (int i = 0; i < 4; ++i) out[i] = v[i];
     return 1;
@@ -112,11 +113,11 @@ def step_layout(f32, n, tiles, *, per_cu=5, lean=False, fill=False, q=0.9, drift
     return dict(per_round=int(out[0]), **{k: x / us for k, x in zip(names, out[1:])})
 
 
-def write_layout(f32, n, tiles, *, per_cu=None, **setting):
+def write_layout(f32, n, tiles, *, per_cu=None, flat=False, **setting):
     """Schedule of a paced broadcast, or None."""
     out = (ctypes.c_double * 4)()
-    ok = _lib().write_layout(_setting(setting), int(f32), per_cu or (16 if f32 else 8), n,
-                             ctypes.c_double(4096.0), ctypes.c_double(4096.0 * (1 if f32 else 2)),
+    ok = _lib().write_layout(_setting(setting), int(f32), int(flat),
+                             per_cu or (16 if f32 else 8), n, ctypes.c_double(4096.0), ctypes.c_double(4096.0 * (1 if f32 else 2)),
                              _i64(tiles), CUS, ctypes.c_double(TICK_HZ), out)
     if not ok:
         return None

@@ -36,3 +36,24 @@ def test_tiles(f32, n, d, L, step, flat):
     assert count == (-(-d // T) if flat else P * -(-L // T))
     # never more partials than the workspace holds, whatever the tiles
     assert count <= P * -(-L // 1024)
+
+
+@pytest.mark.parametrize("f32,flat,n,tiles,paced", [
+    # two rounds (of 2048 bf16 or 1024 fp32 tiles) from 64 workers on
+    (False, False, 64, 2048, False), (False, False, 64, 2049, True),
+    (False, True, 63, 2049, False), (False, True, 64, 2049, True),
+    # one round only with very many workers, and not a short one
+    (False, False, 159, 2048, False), (False, False, 160, 2048, True),
+    (False, False, 160, 1, False), (False, False, 1024, 16, False),
+    (False, False, 160, 819, False), (False, False, 160, 820, True),
+    (False, False, 1024, 159, False), (False, False, 1024, 160, True),
+    (False, True, 160, 271, False), (False, True, 160, 272, True),
+    (False, True, 1024, 100, False),
+    # fp32 rows: eight rounds
+    (True, False, 1024, 7 * 1024, False), (True, False, 64, 7 * 1024 + 1, True),
+    (True, False, 56, 7 * 1024 + 1, False), (True, False, 16, 28 * 1024 + 1, True),
+    (True, False, 15, 40 * 1024, False),
+])
+def test_broadcast_auto_pacing(f32, flat, n, tiles, paced):
+    assert (rules.write_layout(f32, n, tiles, flat=flat) is not None) == paced
+    assert rules.write_layout(f32, n, tiles, flat=flat, mode="always") is not None
