@@ -406,9 +406,10 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * device variable.  Overlapping paced steps on one device can read each
  * other's start time, which costs speed but changes no result.
  * lossy_broadcast is paced by the same setting, as one sweep (auto: bf16 rows
- * from 64 workers and 2 rounds, 24 workers and workers x rounds of 160, or one
- * long enough round of 160 workers; fp32 rows from 16 workers, 8 rounds and
- * workers x rounds of 450), with slots for 1.045 of
+ * from 64 workers and 2 rounds, 24 workers and workers x rounds of 160 (and,
+ * below 40 workers of whole packets, 5.3 rounds), or one long enough round of
+ * 160 workers; fp32 rows from 16 workers, 8 rounds and workers x rounds of
+ * 450), with slots for 1.045 of
  * bytes_per_s (1.0625 of bytes_per_s_f32) and for the share of arrived rows
  * that a small kernel, enqueued before it, samples from the masks.
  * ll_set_pacing returns LL_EINVAL for an unknown mode or a field outside the

@@ -174,9 +174,13 @@ inline bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
 // `places` (masks in memory, p = 0.1, three sets of buffers in turn, unpaced /
 // paced, us):
 //   bf16 rows  N = 64: 3 M (1 round) 70 / 67, 8 M (2) 178 / 160, 26 M 615 / 511
-//              N = 32: 8 M (2) 91 / 93, 16 M (4) 173 / 178, 33 M (8) 406 / 357
-//              N = 24: 13 M (4) 106 / 125, 33 M (8) 319 / 289
+//              N = 40: 14 M (4) 189 / 189, 18 M (5) 245 / 246, 25 M (6) 368 / 322
+//              N = 32: 18 M (5) 196 / 207, 21 M (5.05 rounds) 228 / 239, 22.6 M
+//                      (5.4) 268 / 252, 33 M (8) 401 / 359
+//              N = 28: 21 M (5.05) 200 / 217, 22.6 M (5.4) 228 / 228, 25 M 268 / 245
+//              N = 24: 13 M (4) 106 / 125, 25 M (6.06) 251 / 230, 33 M 310 / 290
 //              N = 16: 50 M (12) 335 / 329
+//              flat tiles, N = 28: 21 M (5.05) 238 / 227;  N = 32: 270 / 251
 //   fp32 rows  N = 64: 8 M (8) 346 / 333, 25 M (24) 1108 / 950
 //              N = 48: 10 M (10) 381 / 352
 //              N = 32: 8 M (8) 175 / 180, 16 M (16) 340 / 333
@@ -199,7 +203,10 @@ inline bool sweep_pays(bool f32_rows, bool flat, int n, int64_t tiles, int64_t p
     if (rounds < 2)
         return n >= kSweepOneRoundRows &&
                (flat ? tiles >= 272 : tiles >= 160 && n * tiles >= 131072);
-    return n >= 64 || (n >= 24 && n * rounds >= 160);
+    // (5.3 rounds of few rows on chunk tiles: shorter ones are served well
+    // unpaced, up to 5.8 TB/s)
+    return n >= 64 || (n >= 24 && n * rounds >= 160 &&
+                       (flat || n >= 40 || 10 * tiles >= 53 * places));
 }
 
 // The schedule of one sweep of writes over n rows of `row` bytes a tile, after

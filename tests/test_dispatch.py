@@ -49,6 +49,13 @@ def test_tiles(f32, n, d, L, step, flat):
     (False, False, 1024, 159, False), (False, False, 1024, 160, True),
     (False, True, 160, 271, False), (False, True, 160, 272, True),
     (False, True, 1024, 100, False),
+    # fewer workers: by workers x rounds, below 40 on chunk tiles 5.3 rounds
+    (False, False, 24, 6 * 2048, False), (False, False, 24, 6 * 2048 + 1, True),
+    (False, False, 28, 5 * 2048 + 1, False), (False, False, 32, 10854, False),
+    (False, False, 32, 10855, True), (False, False, 39, 4 * 2048 + 1, False),
+    (False, False, 40, 3 * 2048 + 1, True), (False, False, 40, 3 * 2048, False),
+    (False, True, 28, 5 * 2048 + 1, True), (False, True, 28, 5 * 2048, False),
+    (False, True, 32, 4 * 2048 + 1, True), (False, True, 23, 30 * 2048, False),
     # fp32 rows: eight rounds
     (True, False, 1024, 7 * 1024, False), (True, False, 64, 7 * 1024 + 1, True),
     (True, False, 56, 7 * 1024 + 1, False), (True, False, 16, 28 * 1024 + 1, True),
