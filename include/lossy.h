@@ -373,9 +373,7 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *                rounds start half a round apart, so one round's gradient
  *                sweep runs beside the previous round's replica sweep and
  *                each round's lead and gap are covered by the other's
- *                streams.  Steps with fp32 replica rows always stream two
- *                (except with `persistent`), and take 0.4 of gap_us, lead_us
- *                and tail_us.
+ *                streams.
  *   resident     rounds sharing the workgroup places the chip holds at once
  *                (overlap..4; default 1): a round has headroom / resident of
  *                them, and rounds start no closer than a round's length /
@@ -395,6 +393,12 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *                workgroups are 128 threads with two loads per row each;
  *                measured to keep their schedule at a lower rate; default
  *                6.4e12).
+ * The defaults of overlap, resident, gap_us, lead_us and tail_us are those of
+ * bf16 replica rows.  As long as all five hold them, fp32 replica rows take a
+ * layout of their own, except with `persistent`: two rounds streaming at once
+ * and 0.4 of the three times.  If any of the five is set otherwise, all apply
+ * as they are set to both row types (tail_us 3.001, for one round of fp32
+ * rows at a time).
  * A workgroup that starts behind its round (its place freed late) issues the
  * rows whose slots have passed at once and then keeps the round's slots.
  * The setting is process-wide and read at each call.  A paced step enqueues,

@@ -130,6 +130,16 @@ struct PaceSetting {
     double bytes_per_s_f32;  // rate for steps whose replica rows are fp32
 };
 
+// Whether the layout of the rounds is left at its defaults.  Those are the
+// best of bf16 rows; fp32 rows then take their own (two rounds streaming,
+// kPaceF32Allowance of the times).  A setting that differs in any of the five
+// is taken as it is for both.
+inline bool default_layout(const PaceSetting& st) {
+    return st.overlap == kDefaultPaceOverlap && st.resident == kDefaultPaceResident &&
+           st.gap_us == kDefaultPaceGapUs && st.lead_us == kDefaultPaceLeadUs &&
+           st.tail_us == kDefaultPaceTailUs;
+}
+
 // Pace of a kernel with a single sweep (the broadcast) whose share of arrived
 // rows the host does not know (see SweepPace).
 struct SweepParams {
@@ -214,7 +224,8 @@ inline bool sweep_pays(bool f32_rows, bool flat, int n, int64_t tiles, int64_t p
 inline bool sweep_layout(const PaceSetting& st, bool f32_rows, bool flat, int per_cu, int n,
                          double row, double in, int64_t tiles, int cus, double tick_hz,
                          SweepParams* q, uint64_t* margin) {
-    const int k = st.overlap > 1 || f32_rows ? 2 : 1;
+    const bool pair = f32_rows && default_layout(st);
+    const int k = st.overlap > 1 || pair ? 2 : 1;
     const int res = st.resident < k ? k : st.resident;
     int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);
     if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
@@ -226,7 +237,7 @@ inline bool sweep_layout(const PaceSetting& st, bool f32_rows, bool flat, int pe
     const double rate =
         f32_rows ? kPaceWriteRateF32 * st.bytes_per_s_f32 : kPaceWriteRate * st.bytes_per_s;
     const double fp = 256.0 * tick_hz * k / rate;
-    const double us = 1e-6 * tick_hz * 256.0 * (f32_rows ? kPaceF32Allowance : 1.0);
+    const double us = 1e-6 * tick_hz * 256.0 * (pair ? kPaceF32Allowance : 1.0);
     const double slot = g * row * fp;
     const double off = st.lead_us * us + g * in * fp;
     const double fixed = off + st.tail_us * us;
@@ -271,10 +282,10 @@ inline bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per
     // streams 4 MiB; rounds of all places were measured slower), so the
     // other half takes the next round while one streams: two rounds stream at
     // once, and since each covers the other's lead, gap and tail, 0.4 of
-    // those is enough.  Rounds of bf16-row kernels take every place (1280
-    // with drift, 1536 without): two rounds at once fall behind their
-    // schedule there.
-    const bool pair = f32_rows && !lean;
+    // those is enough (unless the caller sets a layout of its own).  Rounds of
+    // bf16-row kernels take every place (1280 with drift, 1536 without): two
+    // rounds at once fall behind their schedule there.
+    const bool pair = f32_rows && !lean && default_layout(st);
     const double rate = f32_rows ? st.bytes_per_s_f32 : st.bytes_per_s;
     const int k = st.overlap > 1 || pair ? 2 : 1;
     const int res = st.resident < k ? k : st.resident;

@@ -64,3 +64,49 @@ def test_tiles(f32, n, d, L, step, flat):
 def test_broadcast_auto_pacing(f32, flat, n, tiles, paced):
     assert (rules.write_layout(f32, n, tiles, flat=flat) is not None) == paced
     assert rules.write_layout(f32, n, tiles, flat=flat, mode="always") is not None
+
+
+def _bytes_us(tiles_bytes, k, rate):
+    return tiles_bytes * k / rate * 1e6
+
+
+@pytest.mark.parametrize("over,k,times", [
+    (dict(), 2, (1.6, 0.8, 1.2)),                         # the defaults of fp32 rows
+    (dict(headroom=0.9, bytes_per_s_f32=6.0e12), 2, (1.6, 0.8, 1.2)),
+    # a layout that the caller sets is taken as it is
+    (dict(tail_us=3.001), 1, (4.0, 2.0, 3.001)),
+    (dict(lead_us=3.0), 1, (3.0, 2.0, 3.0)),
+    (dict(gap_us=0.0), 1, (4.0, 0.0, 3.0)),
+    (dict(resident=2), 1, (4.0, 2.0, 3.0)),
+    (dict(overlap=2, resident=2), 2, (4.0, 2.0, 3.0)),
+])
+def test_layout_of_fp32_rows(over, k, times):
+    n, tiles, q = 64, 49_152, 0.9
+    st = {**rules.defaults(), **over}
+    lead, gap, tail = times
+    lay = rules.step_layout(True, n, tiles, per_cu=8, q=q, mode="always", **over)
+    g, rate = lay["per_round"], st["bytes_per_s_f32"]
+    assert g == (1024 if st["headroom"] == 1.0 else -(-tiles // -(-tiles // 921)))
+    state = _bytes_us(g * 4096 * 3, k, rate)
+    close = lambda a, b: abs(a - b) <= 0.01 + 1e-6 * b  # noqa: E731
+    assert close(lay["off_g"], lead + state)
+    assert close(lay["dg"], _bytes_us(g * 4096 * q, k, rate))
+    assert close(lay["off_r"], lay["off_g"] + n * lay["dg"] + state + gap)
+    length = lay["off_s"] + n * lay["ds"] + tail
+    assert close(lay["round"], max((length - lead - gap - tail) / k,
+                                   length / max(k, int(st["resident"]))))
+    sweep = rules.write_layout(True, n, tiles, mode="always", **over)
+    state = _bytes_us(sweep["per_round"] * 4096, k, 1.0625 * rate)
+    assert close(sweep["off"], lead + state) and close(sweep["fixed"], lead + tail + state)
+    assert close(sweep["slot"], _bytes_us(sweep["per_round"] * 4096, k, 1.0625 * rate))
+
+
+def test_layout_of_bf16_and_persistent_rows_is_as_set():
+    for over, k in ((dict(), 1), (dict(lead_us=3.0), 1), (dict(overlap=2, resident=2), 2)):
+        st = {**rules.defaults(), **over}
+        lay = rules.step_layout(False, 64, 25_696, mode="always", **over)
+        rate = st["bytes_per_s"]
+        assert abs(lay["off_g"] - st["lead_us"]
+                   - _bytes_us(lay["per_round"] * 8192 * 3, k, rate)) < 0.01
+    lean = rules.step_layout(True, 64, 49_152, per_cu=4, lean=True, mode="always", persistent=1)
+    assert abs(lean["off_g"] - 4.0 - _bytes_us(lean["per_round"] * 4096 * 3, 1, 6.4e12)) < 0.01
