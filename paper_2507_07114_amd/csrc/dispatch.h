@@ -147,9 +147,21 @@ struct SweepParams {
     uint64_t fixed;        // of a round besides its slots, 1/256 ticks
     uint64_t off;          // first slot after the round's start, 1/256 ticks
     uint64_t slot;         // slot length if every row arrived, 1/256 ticks
+    uint64_t vectors;      // time of the vectors' bytes, 1/256 ticks
     uint64_t rows, share;  // rows; rounds that share the places
+    uint64_t streams;      // rounds streaming at once
     uint64_t guard;        // ticks
 };
+
+// Time between round starts if a row's slot lasts `delta`: no less than the
+// round's bytes take at its share of the rate, and enough for its places to be
+// free again (as in pace_layout).  Evaluated on the device, where the share of
+// arrived rows is known.
+constexpr uint64_t sweep_spacing(const SweepParams& q, uint64_t delta) {
+    const uint64_t places = (q.fixed + q.rows * delta) / q.share;
+    const uint64_t stream = (q.vectors + q.rows * delta) / q.streams;
+    return stream > places ? stream : places;
+}
 
 // Whether LL_PACE_AUTO paces a step of n rows in `rounds` rounds.  Many rows
 // gain most: unpaced, the chip reads pieces of all of them at once.  Few rounds
@@ -246,8 +258,10 @@ inline bool sweep_layout(const PaceSetting& st, bool f32_rows, bool flat, int pe
     q->fixed = (uint64_t)fixed;
     q->off = (uint64_t)off;
     q->slot = (uint64_t)slot;
+    q->vectors = (uint64_t)(g * in * fp);
     q->rows = (uint64_t)n;
     q->share = (uint64_t)res;
+    q->streams = (uint64_t)k;
     *margin = (uint64_t)(kPaceMarginUs * 1e-6 * tick_hz) + 1;
     q->guard = 2 * ((uint64_t)(fixed + n * slot) >> 8) + 2 * *margin + 1;
     return true;

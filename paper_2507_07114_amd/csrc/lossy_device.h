@@ -627,8 +627,7 @@ struct SweepPace {
     // after a barrier that follows fetch()
     __device__ __forceinline__ void begin() {
         delta = uniform64((q.slot * anchor->arrived) >> 16);
-        const uint64_t length = (q.fixed + q.rows * delta) / q.share;
-        base = uniform64(anchor->start) + ((round * length + q.off) >> 8);
+        base = uniform64(anchor->start) + ((round * sweep_spacing(q, delta) + q.off) >> 8);
     }
     __device__ __forceinline__ void row(int i) const {
         wait_until(base + (((uint64_t)i * delta) >> 8), q.guard);

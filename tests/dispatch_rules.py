@@ -48,8 +48,9 @@ int write_layout(const double* st, int f32, int flat, int per_cu, int n, double 
     uint64_t margin;
     if (!sweep_layout(setting(st), f32, flat, per_cu, n, row, in, tiles, cus, hz, &q, &margin))
         return 0;
-    const double v[] = {(double)q.per_round, (double)q.fixed, (double)q.off, (double)q.slot};
-    for (int i = 0; i < 4; ++i) out[i] = v[i];
+    const double v[] = {(double)q.per_round, (double)q.fixed, (double)q.off, (double)q.slot,
+                        (double)sweep_spacing(q, q.slot), (double)sweep_spacing(q, 0)};
+    for (int i = 0; i < 6; ++i) out[i] = v[i];
     return 1;
 }
 }
@@ -114,12 +115,14 @@ def step_layout(f32, n, tiles, *, per_cu=5, lean=False, fill=False, q=0.9, drift
 
 
 def write_layout(f32, n, tiles, *, per_cu=None, flat=False, **setting):
-    """Schedule of a paced broadcast, or None."""
-    out = (ctypes.c_double * 4)()
+    """Schedule of a paced broadcast, or None (round: time between round starts
+    if every row arrives; empty: if none does)."""
+    out = (ctypes.c_double * 6)()
     ok = _lib().write_layout(_setting(setting), int(f32), int(flat),
                              per_cu or (16 if f32 else 8), n, ctypes.c_double(4096.0), ctypes.c_double(4096.0 * (1 if f32 else 2)),
                              _i64(tiles), CUS, ctypes.c_double(TICK_HZ), out)
     if not ok:
         return None
     us = 256.0 * TICK_HZ * 1e-6
-    return dict(per_round=int(out[0]), **{k: x / us for k, x in zip(("fixed", "off", "slot"), out[1:])})
+    names = ("fixed", "off", "slot", "round", "empty")
+    return dict(per_round=int(out[0]), **{k: x / us for k, x in zip(names, out[1:])})

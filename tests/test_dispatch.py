@@ -110,3 +110,18 @@ def test_layout_of_bf16_and_persistent_rows_is_as_set():
                    - _bytes_us(lay["per_round"] * 8192 * 3, k, rate)) < 0.01
     lean = rules.step_layout(True, 64, 49_152, per_cu=4, lean=True, mode="always", persistent=1)
     assert abs(lean["off_g"] - 4.0 - _bytes_us(lean["per_round"] * 4096 * 3, 1, 6.4e12)) < 0.01
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("over", [dict(), dict(resident=2), dict(resident=4),
+                                  dict(overlap=2, resident=2), dict(overlap=2, resident=4),
+                                  dict(tail_us=0.0, lead_us=0.0)])
+def test_broadcast_never_asks_for_more_than_its_rate(f32, over):
+    # the bytes of a round, over the time between round starts, against the rate
+    n, tiles = 64, 24_000
+    lay = rules.write_layout(f32, n, tiles, mode="always", **over)
+    rate = 1.0625 * 6.4e12 if f32 else 1.045 * 6.7e12
+    row, vec = 4096, 4096 * (1 if f32 else 2)
+    asked = lay["per_round"] * (n * row + vec) / (lay["round"] * 1e-6)
+    assert asked <= rate * (1 + 1e-3)  # slots are whole 1/256 ticks
+    assert lay["empty"] >= lay["per_round"] * vec / rate * 1e6 * (1 - 1e-3)
