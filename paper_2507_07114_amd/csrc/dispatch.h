@@ -163,6 +163,17 @@ constexpr uint64_t sweep_spacing(const SweepParams& q, uint64_t delta) {
     return stream > places ? stream : places;
 }
 
+// What one tile of a paced kernel is expected to move: bytes per row slot of
+// each sweep, and of master and moments before and after the first sweep.
+struct PaceTile {
+    int n;
+    bool fill;   // stale fill
+    bool flat;   // flat tiles
+    bool drift;  // with drift
+    double grad, rep, stale;
+    double in, out;
+};
+
 // Whether LL_PACE_AUTO paces a step of n rows in `rounds` rounds.  Many rows
 // gain most: unpaced, the chip reads pieces of all of them at once.  Few rounds
 // lose the start and the end of the schedule, and few rows make rounds so short
@@ -184,7 +195,19 @@ constexpr uint64_t sweep_spacing(const SweepParams& q, uint64_t delta) {
 //              N = 16: 16 M 425 / 440, 33 M (32) 932 / 856
 //              N = 12: 33 M 727 / 694;  N = 8: 33 M 530 / 531, 100 M 1485 / 1538
 //   stale fill, fp32 rows  N = 32: 16 M 1129 / 1144
-inline bool pace_pays(bool f32_rows, bool fill, int n, int64_t rounds) {
+// Flat tiles with drift gain nothing at any size: their stale rows are read
+// vector by vector, so that the last sweep is no stream (bf16 rows, L = 750: N =
+// 32 10 M 319 / 334, 80 M 2357 / 2369; N = 48 6.4 M 273 / 307; N = 64 5 M 284 /
+// 314, 13 M 727 / 750, 80 M 4371 / 4493; N = 96 26 M 2119 / 2168; N = 300 5 M
+// 1257 / 1337; L = 256, N = 64 16 M 878 / 931; L = 6000 866 / 868; fp32 rows, L =
+// 750: N = 16 26 M 756 / 768, N = 64 8 M 832 / 848, 40 M 4126 / 4124).  Without
+// drift they gain like chunks for the most part (L = 750: N = 32 10 M 290 / 270,
+// N = 64 8 M 416 / 366, 13 M 680 / 698, 80 M 4131 / 4175, N = 96 13 M 1005 / 1035;
+// L = 2250, N = 64 16 M 827 / 703; fp32 rows, N = 16 50 M 1399 / 1227).
+inline bool pace_pays(bool f32_rows, const PaceTile& w, int64_t rounds) {
+    const int n = w.n;
+    const bool fill = w.fill;
+    if (w.flat && w.drift) return false;
     if (f32_rows)
         return (n >= 48 && rounds >= 8) ||
                (!fill && ((n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24)));
@@ -267,15 +290,6 @@ inline bool sweep_layout(const PaceSetting& st, bool f32_rows, bool flat, int pe
     return true;
 }
 
-// What one tile of a paced kernel is expected to move: bytes per row slot of
-// each sweep, and of master and moments before and after the first sweep.
-struct PaceTile {
-    int n;
-    bool fill;  // stale fill
-    double grad, rep, stale;
-    double in, out;
-};
-
 // Lay out the schedule of a paced kernel with `tiles` tiles, `per_cu`
 // workgroups of it resident per compute unit, or return false to run it
 // unpaced.  `overlap` rounds stream at once, each covering *grid
@@ -307,7 +321,7 @@ inline bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per
     if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
     if (gmax < 1) return false;
     const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w.fill, w.n, rounds)) return false;
+    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w, rounds)) return false;
     const int64_t g = (tiles + rounds - 1) / rounds;
     const double fp = 256.0 * tick_hz * k / rate;             // 1/256 ticks per byte of a round
     const double allow = pair ? kPaceF32Allowance : 1.0;

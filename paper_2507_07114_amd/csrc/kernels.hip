@@ -1423,6 +1423,8 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     // mix of reads and writes keeps 6.2e12 where the other sweeps keep 6.7e12
     // (N = 64, 8 M: 577 us at 6.2e12, 590 at 6.4e12, 625 at 5.6e12).
     w.fill = p.var.kind == kEstStaleFill;
+    w.flat = p.slots > 0;
+    w.drift = DRIFT;
     w.grad = row_g * (w.fill ? kPaceFillCost * (1.0 + qg) : qg);
     w.rep = row_r * qb;
     w.stale = DRIFT ? row_r * (1.0 - qb) : 0.0;

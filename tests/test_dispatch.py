@@ -66,6 +66,32 @@ def test_broadcast_auto_pacing(f32, flat, n, tiles, paced):
     assert rules.write_layout(f32, n, tiles, flat=flat, mode="always") is not None
 
 
+# places of a round: 5 workgroups of bf16 rows with drift on each of 256
+# compute units, 6 without, 1024 tiles of fp32 rows
+@pytest.mark.parametrize("f32,n,tiles,kw,paced", [
+    (False, 64, 2 * 1280, {}, False), (False, 64, 2 * 1280 + 1, {}, True),
+    (False, 63, 3 * 1280, {}, False), (False, 48, 3 * 1280 + 1, {}, True),
+    (False, 47, 4 * 1280, {}, False), (False, 32, 4 * 1280 + 1, {}, True),
+    (False, 31, 80 * 1280, {}, False),
+    (False, 64, 2 * 1536 + 1, dict(per_cu=6, drift=False), True),
+    (True, 48, 7 * 1024, {}, False), (True, 48, 7 * 1024 + 1, {}, True),
+    (True, 32, 15 * 1024 + 1, {}, True), (True, 32, 15 * 1024 + 1, dict(fill=True), False),
+    (True, 12, 23 * 1024, {}, False), (True, 12, 23 * 1024 + 1, {}, True),
+    (True, 11, 99 * 1024, {}, False),
+    # flat tiles: never with drift
+    (False, 64, 40_000, dict(flat=True, per_cu=4), False),
+    (False, 300, 40_000, dict(flat=True, per_cu=4), False),
+    (False, 64, 40_000, dict(flat=True, per_cu=4, fill=True), False),
+    (True, 64, 40_000, dict(flat=True, per_cu=8), False),
+    (False, 64, 40_000, dict(flat=True, per_cu=5, drift=False), True),
+    (True, 16, 40_000, dict(flat=True, per_cu=8, drift=False), True),
+])
+def test_step_auto_pacing(f32, n, tiles, kw, paced):
+    kw = {**(dict(per_cu=8) if f32 else {}), **kw}
+    assert (rules.step_layout(f32, n, tiles, **kw) is not None) == paced
+    assert rules.step_layout(f32, n, tiles, mode="always", **kw) is not None
+
+
 def _bytes_us(tiles_bytes, k, rate):
     return tiles_bytes * k / rate * 1e6
 
