@@ -354,8 +354,8 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * step runs at the set rate.
  *   mode         LL_PACE_AUTO (default): paced where it was measured to pay,
  *                by the number of workers and of rounds (bf16 rows: from 64
- *                workers and 3 rounds, 48 and 4 or 32 and 5, stale fill 32
- *                and 3; fp32 rows: 48 and 8 and, but for stale fill, 32 and
+ *                workers and 3 rounds, 48 and 4 or 32 and 5, stale fill 32,
+ *                3 and workers x tiles of 115000; fp32 rows: 48 and 8 and, but for stale fill, 32 and
  *                16 or 12 and 24; never with drift where packets do not fill
  *                whole chunks); LL_PACE_ALWAYS; LL_PACE_NEVER.
  *                A round takes every resident workgroup place (bf16

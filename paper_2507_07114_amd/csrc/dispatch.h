@@ -188,13 +188,23 @@ struct PaceTile {
 //              N = 16: 16 M 270 / 287, 100 M 1515 / 1646
 //   stale fill, bf16 rows
 //              N = 64: 8 M (4) 617 / 577, 26 M 1856 / 1783
-//              N = 32: 8 M without drift (3) 317 / 301;  N = 16: 33 M 684 / 767
+//              with drift (rounds in the table are of 1280 tiles), three rounds:
+//              N = 32: 5.3 M 211 / 226, 6 M 237 / 245, 7 M 274 / 276, 7.4 M 301 / 290
+//              N = 40: 5.3 M 259 / 268, 5.9 M 286 / 289, 7 M 339 / 330
+//              N = 48: 5.3 M 308 / 311, 5.6 M 324 / 322, 7 M 401 / 381
+//              four: N = 32 7.9 M 318 / 320, 8.4 M 358 / 332, 20 M (8) 826 / 751
+//              without (of 1536), three: N = 32 7 M 259 / 263, 7.4 M 280 / 276, 8 M
+//              306 / 291;  N = 36: 6.3 M 263 / 269, 7 M 289 / 289, 7.9 M 336 / 319;
+//              N = 48: 7 M 380 / 367;  N = 16: 33 M with drift 684 / 767
 //   fp32 rows  N = 64: 4 M (4) 382 / 425, 8 M (8) 802 / 756, 50 M 4725 / 4220
 //              N = 32: 8 M (8) 412 / 413, 16 M (16) 844 / 769
 //              N = 24: 16 M (16) 598 / 605, 25 M (24) 1035 / 908
 //              N = 16: 16 M 425 / 440, 33 M (32) 932 / 856
 //              N = 12: 33 M 727 / 694;  N = 8: 33 M 530 / 531, 100 M 1485 / 1538
 //   stale fill, fp32 rows  N = 32: 16 M 1129 / 1144
+// Three rounds of stale fill gain from 115000 row tiles on, by rows and tiles
+// alike; on flat tiles (without drift) from three rounds (L = 750: N = 32 5.3 M 213
+// / 210, 7.4 M 295 / 285, but 6.3 M 246 / 257; N = 40 5.3 M 265 / 250).
 // Flat tiles with drift gain nothing at any size: their stale rows are read
 // vector by vector, so that the last sweep is no stream (bf16 rows, L = 750: N =
 // 32 10 M 319 / 334, 80 M 2357 / 2369; N = 48 6.4 M 273 / 307; N = 64 5 M 284 /
@@ -204,7 +214,8 @@ struct PaceTile {
 // drift they gain like chunks for the most part (L = 750: N = 32 10 M 290 / 270,
 // N = 64 8 M 416 / 366, 13 M 680 / 698, 80 M 4131 / 4175, N = 96 13 M 1005 / 1035;
 // L = 2250, N = 64 16 M 827 / 703; fp32 rows, N = 16 50 M 1399 / 1227).
-inline bool pace_pays(bool f32_rows, const PaceTile& w, int64_t rounds) {
+constexpr int64_t kFillRowTiles = 115000;
+inline bool pace_pays(bool f32_rows, const PaceTile& w, int64_t tiles, int64_t rounds) {
     const int n = w.n;
     const bool fill = w.fill;
     if (w.flat && w.drift) return false;
@@ -212,7 +223,7 @@ inline bool pace_pays(bool f32_rows, const PaceTile& w, int64_t rounds) {
         return (n >= 48 && rounds >= 8) ||
                (!fill && ((n >= 32 && rounds >= 16) || (n >= 12 && rounds >= 24)));
     return (n >= 64 && rounds >= 3) || (n >= 48 && rounds >= 4) || (n >= 32 && rounds >= 5) ||
-           (fill && n >= 32 && rounds >= 3);
+           (fill && n >= 32 && rounds >= 3 && (w.flat || n * tiles >= kFillRowTiles));
 }
 
 // Whether LL_PACE_AUTO paces a broadcast of `tiles` tiles in rounds of at most
@@ -321,7 +332,7 @@ inline bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per
     if (f32_rows && gmax > kPaceMaxRoundTiles) gmax = kPaceMaxRoundTiles;
     if (gmax < 1) return false;
     const int64_t rounds = (tiles + gmax - 1) / gmax;
-    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w, rounds)) return false;
+    if (st.mode == kPaceAuto && !pace_pays(f32_rows, w, tiles, rounds)) return false;
     const int64_t g = (tiles + rounds - 1) / rounds;
     const double fp = 256.0 * tick_hz * k / rate;             // 1/256 ticks per byte of a round
     const double allow = pair ? kPaceF32Allowance : 1.0;

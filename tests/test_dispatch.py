@@ -78,6 +78,14 @@ def test_broadcast_auto_pacing(f32, flat, n, tiles, paced):
     (True, 32, 15 * 1024 + 1, {}, True), (True, 32, 15 * 1024 + 1, dict(fill=True), False),
     (True, 12, 23 * 1024, {}, False), (True, 12, 23 * 1024 + 1, {}, True),
     (True, 11, 99 * 1024, {}, False),
+    # stale fill: three rounds, long enough ones
+    (False, 32, 2588, dict(fill=True), False), (False, 32, 3593, dict(fill=True), False),
+    (False, 32, 3594, dict(fill=True), True), (False, 47, 2561, dict(fill=True), True),
+    (False, 44, 2561, dict(fill=True), False), (False, 47, 2560, dict(fill=True), False),
+    (False, 32, 3594, dict(fill=True, per_cu=6, drift=False), True),
+    (False, 36, 3077, dict(fill=True, per_cu=6, drift=False), False),
+    (False, 64, 2561, dict(fill=True), True), (False, 31, 9999, dict(fill=True), False),
+    (False, 32, 2561, dict(fill=True, drift=False, flat=True), True),
     # flat tiles: never with drift
     (False, 64, 40_000, dict(flat=True, per_cu=4), False),
     (False, 300, 40_000, dict(flat=True, per_cu=4), False),
