@@ -362,7 +362,8 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *                rows) or half of them, at most 1024 tiles (fp32 rows, 4 MiB
  *                of a row per slot).
  *   bytes_per_s  rate the slots are laid out for (default 6.7e12), for
- *                steps whose replica rows are bf16.
+ *                steps whose replica rows are bf16; 0.9 of it where their
+ *                gradient rows are fp32.
  *   gap_us       time between the last gradient slot and the first replica
  *                slot, besides the master and moment writes (default 2).
  *   lead_us      time from a round's start to its first gradient slot,

@@ -100,6 +100,15 @@ enum { kPaceAuto = 0, kPaceAlways = 1, kPaceNever = 2 };
 constexpr int64_t kPaceMaxRoundTiles = 1024;  // of fp32-row kernels
 constexpr double kPaceF32Allowance = 0.4;
 constexpr double kPaceFillCost = 1.08;  // time of a stale-fill sweep byte, in plain ones
+// fp32 gradients under bf16 replicas: a thread's two loads of a row touch half
+// lines each, so such a row is read with the plain policy and keeps 6.0e12 (0.9
+// of the rate).  Unpaced, 6.7e12 (not kept), 6.3e12, 6.0e12, us, two cards:
+//   with drift     N = 64 8 M 618 / 622 / 592 / 579, 26 M 1966 / 1955 / 1736-1870 /
+//                  1788, 60 M 4521 / 4511 / 3972-4102 / 4080;  N = 48 20 M 1175 /
+//                  1183 / 1141 / 1080;  N = 32 20 M 814 / 820 / 744-803 / 776
+//   without drift  N = 64 60 M 4367 / 4345 / 3915-4052 / 3931;  N = 48 20 M 1128 /
+//                  1135 / 1100 / 1030;  N = 32 10.6 M 407 / 422 / 417 / 410
+constexpr double kPaceUnlikeRate = 0.9;
 // A broadcast by itself, in rates of a step: 7.0e12 (N = 64, 26 M bf16: 511 us,
 // 6.7e12 531, 6.0e12 585) and 6.8e12.
 constexpr double kPaceWriteRate = 1.045;
@@ -167,9 +176,10 @@ constexpr uint64_t sweep_spacing(const SweepParams& q, uint64_t delta) {
 // each sweep, and of master and moments before and after the first sweep.
 struct PaceTile {
     int n;
-    bool fill;   // stale fill
-    bool flat;   // flat tiles
-    bool drift;  // with drift
+    bool fill;    // stale fill
+    bool flat;    // flat tiles
+    bool drift;   // with drift
+    bool unlike;  // fp32 gradients, bf16 replicas
     double grad, rep, stale;
     double in, out;
 };
@@ -325,7 +335,9 @@ inline bool pace_layout(const PaceSetting& st, bool f32_rows, bool lean, int per
     // bf16-row kernels take every place (1280 with drift, 1536 without): two
     // rounds at once fall behind their schedule there.
     const bool pair = f32_rows && !lean && default_layout(st);
-    const double rate = f32_rows ? st.bytes_per_s_f32 : st.bytes_per_s;
+    const double rate = f32_rows   ? st.bytes_per_s_f32
+                        : w.unlike ? kPaceUnlikeRate * st.bytes_per_s
+                                   : st.bytes_per_s;
     const int k = st.overlap > 1 || pair ? 2 : 1;
     const int res = st.resident < k ? k : st.resident;
     int64_t gmax = (int64_t)(st.headroom * per_cu * cus / res);

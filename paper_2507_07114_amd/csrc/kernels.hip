@@ -1425,6 +1425,7 @@ static bool pace_plan(const PaceSetting& st, bool lean, const FusedParams& p, co
     w.fill = p.var.kind == kEstStaleFill;
     w.flat = p.slots > 0;
     w.drift = DRIFT;
+    w.unlike = sizeof(typename G::T) == 4 && !kF32Rows;
     w.grad = row_g * (w.fill ? kPaceFillCost * (1.0 + qg) : qg);
     w.rep = row_r * qb;
     w.stale = DRIFT ? row_r * (1.0 - qb) : 0.0;

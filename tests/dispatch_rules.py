@@ -28,11 +28,11 @@ void tiles(int f32, int n, int64_t d, int64_t L, int step, int64_t* out) {
     out[0] = t.tiles; out[1] = t.slots;
 }
 int step_layout(const double* st, int f32, int lean, int flat, int per_cu, int n, int fill,
-                int drift, double grad, double rep, double stale, double in, int64_t tiles, int cus,
-                double hz, double* out) {
+                int drift, int unlike, double grad, double rep, double stale, double in,
+                int64_t tiles, int cus, double hz, double* out) {
     PaceTile w;
     w.n = n; w.fill = fill; w.flat = flat; w.drift = drift;
-    w.grad = grad; w.rep = rep; w.stale = stale; w.in = w.out = in;
+    w.unlike = unlike; w.grad = grad; w.rep = rep; w.stale = stale; w.in = w.out = in;
     PaceParams q;
     int64_t grid;
     uint64_t margin;
@@ -97,14 +97,14 @@ def tiles(f32, n, d, L, step=True):
     return out[0], out[1]
 
 
-def step_layout(f32, n, tiles, *, per_cu=5, lean=False, flat=False, fill=False, q=0.9, drift=True,
-                vectors=3, **setting):
+def step_layout(f32, n, tiles, *, per_cu=5, lean=False, flat=False, fill=False, unlike=False,
+                q=0.9, drift=True, vectors=3, **setting):
     """Schedule of a paced step (times in us, rounds in tiles), or None."""
     row = 4096.0
     out = (ctypes.c_double * 8)()
-    grad = row * (1.08 * (1 + q) if fill else q)
+    grad = row * (1.08 * (1 + q) if fill else q) * (2 if unlike else 1)
     ok = _lib().step_layout(_setting(setting), int(f32), int(lean), int(flat), per_cu, n,
-                            int(fill), int(drift), ctypes.c_double(grad), ctypes.c_double(row * q),
+                            int(fill), int(drift), int(unlike), ctypes.c_double(grad), ctypes.c_double(row * q),
                             ctypes.c_double(row * (1 - q) if drift else 0.0),
                             ctypes.c_double(row * vectors * (1 if f32 else 2)), _i64(tiles), CUS,
                             ctypes.c_double(TICK_HZ), out)

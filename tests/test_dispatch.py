@@ -135,6 +135,16 @@ def test_layout_of_fp32_rows(over, k, times):
     assert close(sweep["slot"], _bytes_us(sweep["per_round"] * 4096, k, 1.0625 * rate))
 
 
+def test_fp32_gradients_under_bf16_replicas_take_a_lower_rate():
+    n, tiles = 64, 25_696
+    like, unlike = (rules.step_layout(False, n, tiles, unlike=u) for u in (False, True))
+    g = like["per_round"]
+    assert unlike["per_round"] == g
+    assert abs(like["dg"] - _bytes_us(g * 4096 * 0.9, 1, 6.7e12)) < 0.01
+    assert abs(unlike["dg"] - _bytes_us(2 * g * 4096 * 0.9, 1, 0.9 * 6.7e12)) < 0.01
+    assert abs(unlike["dr"] - like["dr"] / 0.9) < 0.01
+
+
 def test_layout_of_bf16_and_persistent_rows_is_as_set():
     for over, k in ((dict(), 1), (dict(lead_us=3.0), 1), (dict(overlap=2, resident=2), 2)):
         st = {**rules.defaults(), **over}
