@@ -49,7 +49,15 @@ constexpr size_t flat_lds_bytes(int ndir, int slots, int n) {
 // they are so few that most run at once: then the time is one tile's, and a
 // flat tile's code is the longer one (N = 64 bf16, L = 256: 0.2 M 30 / 49 with
 // 782 chunk tiles, 0.8 M 85 / 63 with 3125; N = 16: 20 / 23 and 46 / 27; fp32
-// N = 64, whose workgroups are half as large: 31 / 53 and 92 / 97).
+// N = 64, whose workgroups are half as large: 31 / 53 and 92 / 97).  Elements of
+// 4 bytes are moved one by one well enough for that to hold of other lengths,
+// too, while packets are short and there are 36 tiles or fewer, 64 of the shortest
+// (fp32 rows, L = 375, 33 K: N = 8 17 / 19, N = 64 42 / 62, N = 96 56 / 88, N = 64
+// aggregate 22 / 27, broadcast 13 / 26, drift 31 / 37; L = 511 42 / 55; L = 65, 66 K:
+// N = 8 19 / 24, N = 64 45 / 85).  Beyond, steps of bf16 gradients under them (L =
+// 375, N = 64: 33 K 60 / 72, 49 K 68 / 60) and an aggregate (L = 100: 33 K 24 / 27, 81
+// K 25 / 23) gain on flat tiles, and a drift pass of longer packets (L = 750, 33 K:
+// 41 / 36); bf16 rows do at once (L = 333, 33 K: N = 16 35 / 29, N = 64 80 / 77).
 constexpr int kFewStepRows = 12;
 // Elements of a tile: 4 KiB of a row.
 constexpr int tile_elems(bool f32_rows) { return f32_rows ? 1024 : 2048; }
@@ -65,7 +73,8 @@ inline TileGrid tile_grid(bool f32_rows, int n, int64_t d, int64_t P, int64_t L,
     const int64_t cpp = (L + T - 1) / T;
     const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
     const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
-    const bool small = L % 8 == 0 && P * cpp <= (f32_rows ? 4096 : 1024);
+    const bool small = L % 8 == 0 ? P * cpp <= (f32_rows ? 4096 : 1024)
+                                  : f32_rows && L <= T / 2 && d <= (L <= T / 8 ? 64 : 36) * T;
     if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small)
         return TileGrid{P * cpp, (int)cpp, 0, 0};
     const int slots = flat_slots(T, L);

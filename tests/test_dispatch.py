@@ -27,6 +27,12 @@ def test_defaults_are_the_bindings():
     (False, 9, 256 * 1025, 256, True, True),
     (True, 2, 72 * 4096, 72, True, False),
     (True, 2, 72 * 4097, 72, True, True),
+    # other lengths: fp32 rows in very few tiles of short packets
+    (True, 64, 36 * 1024, 375, True, False), (True, 64, 36 * 1024 + 1, 375, True, True),
+    (True, 64, 33_001, 512 - 1, True, False), (True, 64, 33_001, 512 + 1, True, True),
+    (True, 8, 64 * 1024, 100, False, False), (True, 8, 64 * 1024 + 1, 100, False, True),
+    (True, 8, 60_000, 129, True, True), (True, 64, 33_001, 63, True, False),
+    (False, 64, 33_001, 375, True, True),
 ])
 def test_tiles(f32, n, d, L, step, flat):
     count, slots = rules.tiles(f32, n, d, L, step)

@@ -13,6 +13,7 @@ import torch
 import paper_2507_07114_amd as ll
 import workloads as wl
 
+import dispatch_rules as rules
 import parity
 from test_gpu_fused import _bit_equal, _snapshot, _stagewise
 from test_gpu_fuzz import OPTS, test_random_configuration as check_configuration
@@ -26,46 +27,62 @@ GE = dict(kind=wl.GILBERT_ELLIOTT, p_gb=0.2, p_bg=0.3, loss_good=0.05, loss_bad=
 
 
 def _case(case, n, packet, d, gdtype, opt, loss=BERN, est="arrived_mean", owner=-1,
-          reliable=False, parity=0, lam=0.0):
+          reliable=False, parity=0, lam=0.0, flat=True):
     return dict(case=case, n=n, packet=packet, d=d, gdtype=gdtype, opt=opt, loss=loss, est=est,
-                owner=owner, reliable=reliable, parity=parity, lam=lam)
+                owner=owner, reliable=reliable, parity=parity, lam=lam, flat=flat)
+
+
+def _tiling(w, rdtype=None, step=True):
+    """Whether a workload's step and drift pass (step=False: an aggregate or a
+    broadcast of such rows by itself) run on flat tiles."""
+    return rules.tiles((rdtype or w.gdtype) == wl.F32, w.n, w.d, w.packet, step)[1] > 0
 
 
 CASES = [
     # the shortest flat packets (33 per tile), and the longest that are not
     _case(2000, 3, 64, 70_001, wl.BF16, "adam"),
-    _case(2001, 3, 63, 4_001, wl.BF16, "adam"),
-    _case(2002, 1, 65, 2_048, wl.F32, "sgd"),
+    _case(2001, 3, 63, 4_001, wl.BF16, "adam", flat=False),
+    _case(2002, 1, 65, 2_048, wl.F32, "sgd", flat=False),
     # Ethernet payloads; owner, reliable and parity packets; empty packets
     _case(2003, 16, 750, 20_011, wl.BF16, "adam", owner=5, reliable=True, parity=4),
     _case(2004, 33, 375, 10_007, wl.F32, "momentum",
-          dict(kind=wl.BERNOULLI, p=0.97), lam=0.1),
+          dict(kind=wl.BERNOULLI, p=0.97), lam=0.1, flat=False),
     _case(2005, 2, 2250, 4_096, wl.BF16, "sgd", dict(kind=wl.BERNOULLI, p=1.0), lam=0.1),
     # Horvitz-Thompson: weights that differ between the packets of a tile
     _case(2006, 20, 100, 6_001, wl.BF16, "adam", est="horvitz_thompson", owner=19, reliable=True,
           parity=3),
     _case(2007, 70, 333, 6_002, wl.F32, "momentum", GE, est="horvitz_thompson", owner=66,
-          reliable=True),
+          reliable=True, flat=False),
     # stale fill: a vector half from the arrived row, half from the last one
     _case(2008, 31, 750, 12_345, wl.BF16, "momentum", est="stale_fill"),
-    _case(2009, 65, 129, 5_003, wl.F32, "sgd", GE, est="stale_fill", reliable=True),
+    _case(2009, 65, 129, 5_003, wl.F32, "sgd", GE, est="stale_fill", reliable=True, flat=False),
     # one element more and less than a tile, and a packet of several tiles
     _case(2010, 8, 2047, 16_384, wl.BF16, "adam"),
     _case(2011, 64, 1025, 16_385, wl.F32, "adam", GE),
     _case(2012, 130, 8191, 30_001, wl.BF16, "adam"),
-    _case(2013, 1024, 204, 3_000, wl.F32, "adam", owner=1000),
+    _case(2013, 1024, 204, 3_000, wl.F32, "adam", owner=1000, flat=False),
+    # the fp32 cases above run on chunk tiles, being so few; the same on flat ones
+    _case(2020, 1, 65, 83_000, wl.F32, "sgd"),
+    _case(2021, 33, 375, 50_011, wl.F32, "momentum",
+          dict(kind=wl.BERNOULLI, p=0.97), lam=0.1),
+    _case(2022, 70, 333, 50_002, wl.F32, "momentum", GE, est="horvitz_thompson", owner=66,
+          reliable=True),
+    _case(2023, 65, 129, 50_003, wl.F32, "sgd", GE, est="stale_fill", reliable=True),
+    _case(2024, 1024, 521, 3_000, wl.F32, "adam", owner=1000),
     # lengths a multiple of 8, flat from 1025 (bf16) or 4097 (fp32) chunk tiles
     # on and chunks up to there
     _case(2014, 9, 256, 256 * 1025 - 200, wl.BF16, "adam"),
-    _case(2015, 9, 256, 256 * 1024, wl.BF16, "adam"),
+    _case(2015, 9, 256, 256 * 1024, wl.BF16, "adam", flat=False),
     _case(2016, 2, 72, 72 * 4097 - 5, wl.F32, "momentum", est="stale_fill"),
     # off the 128-byte lines, flat from 12 rows on in a step
-    _case(2017, 12, 6000, 400_001, wl.BF16, "sgd"),
+    _case(2017, 12, 6000, 400_001, wl.BF16, "sgd", flat=False),
 ]
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"case{c['case']}")
 def test_flat_step_matches_the_oracle(cfg):
+    f32 = cfg["gdtype"] == wl.F32
+    assert (rules.tiles(f32, cfg["n"], cfg["d"], cfg["packet"])[1] > 0) == cfg["flat"]
     check_configuration(cfg)
 
 
@@ -73,6 +90,7 @@ def test_flat_step_matches_the_oracle(cfg):
     ("n8_d16m_bf16_adam", 8, 40_961, 750, 0),
     ("n8_d16m_bf16_adam", 200, 9_001, 250, 8),
     ("n64_d48m_f32_sgd_drift", 64, 20_005, 375, 4),
+    ("n64_d48m_f32_sgd_drift", 64, 50_005, 375, 4),
     ("n16_d256m_f32_ge_momentum", 17, 30_720, 2250, 0),
     # broadcast and aggregate alone on flat tiles, the step on chunks
     ("n8_d16m_bf16_adam", 8, 1_200_000, 1928, 0),
@@ -120,9 +138,12 @@ def test_flat_paced_step_is_bit_identical_to_unpaced(name, n, d, L, masks_out, d
 
 @pytest.mark.parametrize("gdtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("est", ["arrived_mean", "horvitz_thompson", "stale_fill"])
-def test_flat_aggregate_stage(est, gdtype):
+@pytest.mark.parametrize("d", [10_007, 50_007])  # fp32 rows: chunk tiles, flat ones
+def test_flat_aggregate_stage(est, gdtype, d):
     """lossy_aggregate alone: lost elements hold NaN and are never used."""
-    n, d, L = 37, 10_007, 333
+    n, L = 37, 333
+    f32 = gdtype == torch.float32
+    assert (rules.tiles(f32, n, d, L, step=False)[1] > 0) == (d > 50_000 or not f32)
     P = -(-d // L)
     gen = torch.Generator(device=DEV).manual_seed(7)
     arrived = (torch.rand((n, P), generator=gen, device=DEV) < 0.6).to(torch.uint8)
@@ -179,7 +200,8 @@ def test_flat_drift_skips_nonfinite_elements_that_arrived(gdtype, p):
     nothing to the drift where every row holds it, also beside an element of a
     lossy packet in the same vector: such a row's drift is that of the other
     elements."""
-    n, d, L = 5, 10_003, 333  # whole tiles and a ragged end
+    n, d, L = 5, 50_003, 333  # whole tiles and a ragged end
+    assert rules.tiles(gdtype == torch.float32, n, d, L)[1] > 0
     P = -(-d // L)
     print(f"flat nonfinite {gdtype} p={p}", flush=True)
     gen = torch.Generator(device=DEV).manual_seed(3)
