@@ -74,7 +74,7 @@ CASES = [
     _case(2014, 9, 256, 256 * 1025 - 200, wl.BF16, "adam"),
     _case(2015, 9, 256, 256 * 1024, wl.BF16, "adam", flat=False),
     _case(2016, 2, 72, 72 * 4097 - 5, wl.F32, "momentum", est="stale_fill"),
-    # off the 128-byte lines, flat from 12 rows on in a step
+    # off the 128-byte lines, but in few tiles
     _case(2017, 12, 6000, 400_001, wl.BF16, "sgd", flat=False),
 ]
 
@@ -86,17 +86,23 @@ def test_flat_step_matches_the_oracle(cfg):
     check_configuration(cfg)
 
 
-@pytest.mark.parametrize("name,n,d,L,pad", [
-    ("n8_d16m_bf16_adam", 8, 40_961, 750, 0),
-    ("n8_d16m_bf16_adam", 200, 9_001, 250, 8),
-    ("n64_d48m_f32_sgd_drift", 64, 20_005, 375, 4),
-    ("n64_d48m_f32_sgd_drift", 64, 50_005, 375, 4),
-    ("n16_d256m_f32_ge_momentum", 17, 30_720, 2250, 0),
-    # broadcast and aggregate alone on flat tiles, the step on chunks
-    ("n8_d16m_bf16_adam", 8, 1_200_000, 1928, 0),
+# tiles: (of the step and the drift pass, of the aggregate and the broadcast), flat?
+@pytest.mark.parametrize("name,n,d,L,pad,tiles", [
+    ("n8_d16m_bf16_adam", 8, 40_961, 750, 0, (True, True)),
+    ("n8_d16m_bf16_adam", 200, 9_001, 250, 8, (True, True)),
+    ("n64_d48m_f32_sgd_drift", 64, 20_005, 375, 4, (False, False)),
+    ("n64_d48m_f32_sgd_drift", 64, 50_005, 375, 4, (True, True)),
+    ("n16_d256m_f32_ge_momentum", 17, 30_720, 2250, 0, (True, True)),
+    # full chunks off the 128-byte lines: few rows of a step stay with chunks,
+    # stages by themselves do not, and with more rows all are flat
+    ("n8_d16m_bf16_adam", 8, 1_200_000, 1928, 0, (False, False)),
+    ("n8_d16m_bf16_adam", 8, 2_000_003, 1928, 0, (False, True)),
+    ("n8_d16m_bf16_adam", 11, 2_060_001, 6000, 0, (False, True)),
+    ("n8_d16m_bf16_adam", 12, 2_060_001, 6000, 0, (True, True)),
 ])
-def test_flat_step_equals_stagewise(name, n, d, L, pad):
+def test_flat_step_equals_stagewise(name, n, d, L, pad, tiles):
     w = wl.scaled(wl.WORKLOADS[name], n=n, d=d, packet=L)
+    assert (_tiling(w), _tiling(w, step=False)) == tiles
     a, b = parity.DeviceState(w, pad=pad), parity.DeviceState(w, pad=pad)
     for t in range(2):
         print(f"flat {name} n={n} d={d} L={L} step {t}", flush=True)
@@ -112,17 +118,30 @@ def test_flat_step_equals_stagewise(name, n, d, L, pad):
                 assert _bit_equal(sa[k], sb[k]), f"step {t}: {k} differs"
 
 
-@pytest.mark.parametrize("name,n,d,L", [
-    ("n64_llama7b_shard_bf16_adam", 64, 2048 * 2600 + 1009, 750),
-    ("n64_d48m_f32_sgd_drift", 40, 1024 * 5000 + 13, 1500),
+def _with_replicas(w, rdtype):
+    """Two states of a workload whose replica rows are of type rdtype."""
+    out = parity.DeviceState(w), parity.DeviceState(w)
+    for dev in out:
+        dev.replicas = torch.zeros((w.n, dev.ld), dtype=wl.torch_dtype(rdtype), device=DEV)
+        dev.replicas[:, : w.d] = dev.theta.to(dev.replicas.dtype)[None, :]
+    return out
+
+
+@pytest.mark.parametrize("name,n,d,L,rdtype", [
+    ("n64_llama7b_shard_bf16_adam", 64, 2048 * 2600 + 1009, 750, wl.BF16),
+    ("n64_d48m_f32_sgd_drift", 40, 1024 * 5000 + 13, 1500, wl.F32),
+    # rows of unlike types
+    ("n64_llama7b_shard_bf16_adam", 33, 1024 * 2600 + 77, 750, wl.F32),
+    ("n64_d48m_f32_sgd_drift", 33, 2048 * 2600 + 501, 333, wl.BF16),
 ])
 @pytest.mark.parametrize("masks_out,drift", [(True, True), (False, False)])
-def test_flat_paced_step_is_bit_identical_to_unpaced(name, n, d, L, masks_out, drift,
+def test_flat_paced_step_is_bit_identical_to_unpaced(name, n, d, L, rdtype, masks_out, drift,
                                                      restore_pacing):  # noqa: F811
     w = wl.scaled(wl.WORKLOADS[name], n=n, d=d, packet=L)
-    a, b = parity.DeviceState(w), parity.DeviceState(w)
+    assert _tiling(w, rdtype)
+    a, b = _with_replicas(w, rdtype)
     for t in range(2):
-        print(f"flat paced {name} n={n} L={L} step {t}", flush=True)
+        print(f"flat paced {name} n={n} L={L} {rdtype} step {t}", flush=True)
         wl.draw_grads(w, t, device=DEV, ld=a.ld, out=a.grads)
         b.grads.copy_(a.grads)
         ll.ll_set_pacing("always")
@@ -134,6 +153,47 @@ def test_flat_paced_step_is_bit_identical_to_unpaced(name, n, d, L, masks_out, d
         for k in sa:
             if k != "drift" and (masks_out or not k.startswith("arrived")):
                 assert _bit_equal(sa[k], sb[k]), f"step {t}: {k} differs"
+
+
+@pytest.mark.parametrize("gdtype,rdtype", [(wl.BF16, wl.F32), (wl.F32, wl.BF16)])
+@pytest.mark.parametrize("L", [750, 333])
+@pytest.mark.parametrize("est", ["arrived_mean", "horvitz_thompson", "stale_fill"])
+def test_flat_step_of_unlike_row_types_equals_stagewise(est, L, gdtype, rdtype):
+    """The step takes the replicas' tiles for both rows, each stage its own
+    rows': 8-byte halves of bf16 gradient rows and unsplit fp32 ones."""
+    n, d = 20, 83_005
+    w = wl.scaled(wl.WORKLOADS["n8_d16m_bf16_adam"], n=n, d=d, packet=L, gdtype=gdtype,
+                  loss=dict(kind=wl.BERNOULLI, p=0.3))
+    assert _tiling(w, rdtype) and _tiling(w, gdtype, step=False)
+    a, b = _with_replicas(w, rdtype)
+    P, spec = w.num_packets, parity.loss_spec(w)
+    prev = [torch.randn(a.grads.shape, generator=torch.Generator(DEV).manual_seed(1), device=DEV)
+            .to(a.grads.dtype) for _ in range(2)]
+    owner = 3 if est == "horvitz_thompson" else -1
+    ext = [ll.ext(est, owner=owner, g_prev=g if est == "stale_fill" else None,
+                  arrival_prob=0.7 if est == "horvitz_thompson" else 0.0) for g in prev]
+    for t in range(2):
+        print(f"flat unlike {est} {gdtype}/{rdtype} L={L} step {t}", flush=True)
+        wl.draw_grads(w, t, device=DEV, ld=a.ld, out=a.grads)
+        b.grads.copy_(a.grads)
+        a.fused(t, ext=ext[0])
+        g_hat = torch.empty(d, device=DEV)
+        only = ll.ext(owner=owner)
+        ll.ll_masks(n, P, t, ll.LL_DIR_GRAD, spec, b.arrived_g, ext=only)
+        ll.lossy_aggregate(b.grads, b.arrived_g, d=d, packet=L, g_hat=g_hat, counts=b.counts,
+                           theta=b.theta, ext=ext[1])
+        ll.shard_step(parity.opt_spec(w), t, b.theta, g_hat, m=b.m, v=b.v)
+        ll.ll_masks(n, P, t, ll.LL_DIR_BCAST, spec, b.arrived_b, ext=only)
+        ll.lossy_broadcast(b.theta, b.replicas, b.arrived_b, d=d, packet=L)
+        ll.drift_stats(b.replicas, d=d, packet=L, workspace=b.workspace, out=b.drift,
+                       theta=b.theta, arrived_bc=b.arrived_b)
+        sa, sb = _snapshot(a), _snapshot(b)
+        sa["drift"]["empty_packets"] = sb["drift"]["empty_packets"] = 0
+        assert sa["drift"] == sb["drift"], (sa["drift"], sb["drift"])
+        for k in sa:
+            if k != "drift":
+                assert _bit_equal(sa[k], sb[k]), f"step {t}: {k} differs"
+        assert _bit_equal(prev[0], prev[1]), f"step {t}: g_prev differs"
 
 
 @pytest.mark.parametrize("gdtype", [torch.bfloat16, torch.float32])

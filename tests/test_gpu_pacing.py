@@ -7,9 +7,9 @@
   mask outputs or a workspace, under schedules that are kept and schedules
   laid out far too fast to keep, with a workgroup per tile or one round of
   workgroups looping over the rounds.
-* Packets whose length is not a multiple of 8 elements, and fp32 rows whose
-  stride is 4 (mod 8) elements, take the element-by-element access form;
-  they match the oracle and the stage-by-stage chain.
+* Packets whose length is not a multiple of 8 elements (one by one below 64,
+  on flat tiles above, and the shard's ragged end in either) and fp32 rows whose
+  stride is 4 (mod 8) elements match the oracle and the stage-by-stage chain.
 """
 
 import numpy as np
@@ -59,7 +59,8 @@ PACED = {
 }
 
 SCHEDULES = [
-    dict(overlap=1, resident=1, bytes_per_s=6.3e12),   # the default: one round at a time
+    # the default layout: bf16 rows one round at a time, fp32 rows two
+    dict(overlap=1, resident=1, bytes_per_s=6.3e12),
     dict(overlap=2, resident=2, bytes_per_s=6.0e12),   # two rounds streaming at once
     dict(overlap=2, resident=3, bytes_per_s=5.0e14),   # far too fast to keep
     # one round of workgroups looping over the rounds (steps in the plain
@@ -104,7 +105,8 @@ def test_paced_step_is_bit_identical_to_unpaced(name, sched, masks_out, drift, w
 
 
 # ---------------------------------------------------------------------------
-# Element-by-element access: packets not a multiple of 8, fp32 rows at 4 mod 8
+# Packets not a multiple of 8 (1 and 3: element by element, 100 and 4097: flat
+# tiles or, for few fp32 rows, elements), fp32 rows at 4 mod 8
 # ---------------------------------------------------------------------------
 ODD = [
     # (workload, d, packet, pad): pad makes the row stride d rounded to 256 + pad

@@ -1,7 +1,8 @@
 """The paced broadcast (row stores wait for clock slots scaled by the sampled
-share of arrived rows) is bit-identical to the unpaced one, and so are the
-aggregate and drift calls beside it: kept and far too fast, chunk and flat
-tiles, with everything, nothing and some rows arrived."""
+share of arrived rows) is bit-identical to the unpaced one, kept and far too
+fast, on chunk and flat tiles, with everything, nothing and some rows arrived,
+and from a graph.  The aggregate and drift calls beside it read no pacing
+setting; they check that a paced broadcast leaves its neighbours alone."""
 import pytest
 import torch
 
@@ -41,7 +42,8 @@ def _stages(g, reps, theta, arrived, d, L, lam):
     (3, 5_000, 1024, torch.float32),             # fewer tiles than a round
     (20, 2048 * 2300 + 8, 4096, torch.bfloat16),
     (20, 2048 * 2300 + 3, 750, torch.bfloat16),  # flat tiles
-    (70, 1024 * 2100 + 5, 3000, torch.float32),
+    (70, 1024 * 2100 + 5, 3000, torch.float32),  # 2151 chunk tiles, few enough
+    (70, 1024 * 2100 + 5, 1300, torch.float32),  # flat tiles
 ])
 def test_paced_stages_are_bit_identical(n, d, L, dtype, p, sched, restore_pacing):  # noqa: F811
     print(f"paced stages n={n} d={d} L={L} {dtype} p={p} schedule {sched}", flush=True)
@@ -59,3 +61,38 @@ def test_paced_stages_are_bit_identical(n, d, L, dtype, p, sched, restore_pacing
         for name, a, b in zip(("g_hat", "counts", "replicas", "drift", "drift of rows alone"),
                               got, want):
             assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("n,d,L,dtype", [
+    (20, 2048 * 2300 + 8, 4096, torch.bfloat16),
+    (40, 1024 * 2100 + 5, 750, torch.float32),  # flat tiles
+])
+def test_captured_paced_broadcast_replays_like_eager(n, d, L, dtype, restore_pacing):  # noqa: F811
+    print(f"captured broadcast n={n} d={d} L={L} {dtype}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    P, ld = -(-d // L), -(-d // 8) * 8
+    arrived = (torch.rand((n, P), generator=gen, device=DEV) >= 0.3).to(torch.uint8)
+    theta = torch.randn(d, generator=gen, device=DEV)
+    start = torch.randn((n, ld), generator=gen, device=DEV).to(dtype)
+    a, b = start.clone(), start.clone()
+    ll.ll_set_pacing("always")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ll.lossy_broadcast(theta, b, arrived, d=d, packet=L)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ll.lossy_broadcast(theta, b, arrived, d=d, packet=L)
+    ll.ll_set_pacing("never")
+    for rep in range(3):
+        theta.normal_(generator=gen)
+        arrived.copy_(torch.rand((n, P), generator=gen, device=DEV) >= 0.3)
+        a.copy_(start)
+        b.copy_(start)
+        ll.lossy_broadcast(theta, a, arrived, d=d, packet=L)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), f"replay {rep} differs"

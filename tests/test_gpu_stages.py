@@ -254,3 +254,28 @@ def test_drift_identical_replicas_is_zero_and_empty_shard():
     ll.drift_stats(reps, d=0, packet=L, workspace=ws, out=out2)
     r = ll.read_drift(out2)
     assert r["max_abs"] == 0 and r["mean_sq"] == 0 and r["stale_packets"] == 0
+
+
+@pytest.mark.parametrize("kind,vectors", [("sgd", 2), ("momentum", 3), ("adam", 4)])
+@pytest.mark.parametrize("more", [0, 7])
+def test_shard_step_of_streamed_vectors(kind, vectors, more):
+    """Vectors of more than 256 MiB in all are streamed past the caches (the
+    last size that is not, and a ragged one that is): bit-identical to the same
+    update in two slices, and nothing past d is touched."""
+    d = ((256 << 20) // (4 * vectors) & ~3) + more
+    assert (vectors * 4 * d > 256 << 20) == (more > 0)
+    print(f"streamed update {kind} d={d}", flush=True)
+    spec = dict(sgd=ll.sgd(0.01), momentum=ll.sgd_momentum(0.01, 0.9),
+                adam=ll.adam(3e-4, 0.9, 0.95, 1e-8))[kind]
+    gen = torch.Generator(device=DEV).manual_seed(vectors)
+    end = d + 8
+    theta, m, g_hat = (torch.randn(end, generator=gen, device=DEV) for _ in range(3))
+    v = torch.rand(end, generator=gen, device=DEV)
+    want = [x.clone() for x in (theta, m, v)]
+    cut = d // 2 & ~3
+    for part in (slice(0, cut), slice(cut, d)):
+        w_th, w_m, w_v = (x[part] for x in want)
+        ll.shard_step(spec, 7, w_th, g_hat[part], m=w_m, v=w_v, d=w_th.numel())
+    ll.shard_step(spec, 7, theta, g_hat, m=m, v=v, d=d)
+    for name, x, y in zip(("theta", "m", "v"), (theta, m, v), want):
+        assert torch.equal(x, y), name
