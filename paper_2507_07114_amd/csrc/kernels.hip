@@ -855,13 +855,13 @@ __device__ __forceinline__ void step_flat_chunk(const FusedParams& p, const Flat
     const auto slot = [&](int row) { pace.stale(row); };
     // An element that arrived adds nothing: it takes the reference, whose
     // difference from itself is 0 if it is finite.  Wavefronts with another
-    // value, which are rare, go by the elements' masks, one row at a time
-    // (masking every difference took 1 to 4% of a step, and a choice within
-    // one loop 40 VGPRs).
-    bool odd = false;
+    // value, which are rare, and the one ragged tile go by the elements' masks,
+    // one row at a time (masking every difference took 1 to 4% of a step, and a
+    // choice within one loop 40 VGPRs).
+    float zero = 0.0f;  // NaN if a value is not finite
 #pragma unroll
-    for (int j = 0; j < 8; ++j) odd = odd || !(fabsf(rv[j]) < __builtin_inff());
-    if (__any(odd)) {
+    for (int j = 0; j < 8; ++j) zero = __fmaf_rn(rv[j], 0.0f, zero);
+    if (!W || __any(!(zero == 0.0f))) {
         stream_flat<1, R, W>(reps, p.ld_r, ch, stale, slot, [&](const Raw8<R>& raw, uint32_t elems) {
             float x[8];
             unpack(raw, x);
@@ -950,10 +950,8 @@ __device__ __forceinline__ void step_flat(const FusedParams& p, int64_t tile, co
     else step_flat_w<G, R, DRIFT, false>(p, f, tile, pace, lds);
 }
 
-// (4 wavefronts per SIMD: without the bound the sweep of references that are
-// not finite takes fp32 rows to 130-132 VGPRs and 3; with it two are spilled.)
 template <class G, class R, bool DRIFT>
-__global__ __launch_bounds__(R::kPacketThreads, 4) void k_step_flat(FusedParams p) {
+__global__ __launch_bounds__(R::kPacketThreads) void k_step_flat(FusedParams p) {
     step_flat<G, R, DRIFT>(p, blockIdx.x, NoPace());
 }
 
@@ -1008,7 +1006,7 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_step_paced(FusedParams p,
 }
 
 template <class G, class R, bool DRIFT>
-__global__ __launch_bounds__(R::kPacketThreads, 4) void k_step_flat_paced(FusedParams p,
+__global__ __launch_bounds__(R::kPacketThreads) void k_step_flat_paced(FusedParams p,
                                                                        PaceParams q) {
     __shared__ uint64_t s_anchor;
     const ClockPace pace = round_pace(q, (uint64_t)blockIdx.x / (uint64_t)q.per_round, &s_anchor);
