@@ -31,10 +31,11 @@
  *   - Row-major [N][ld] buffers: row i starts at element i * ld.  ld >= D and
  *     ld times the element size (4 bytes fp32, 2 bytes bf16) is a multiple of
  *     16 bytes, so every row starts on a 16-byte boundary.
- *   - Any packet length L >= 1 is accepted.  Packets whose start is a multiple
- *     of 8 elements (L a multiple of 8) are moved with 16-byte vector accesses;
- *     other packets, and the last 1..7 elements of a shard whose D is not a
- *     multiple of 8, are moved element by element (same results, slower).
+ *   - Any packet length L >= 1 is accepted, with the same results.  Lengths that
+ *     are a multiple of 8 elements, and of the others those of 64 elements or
+ *     more, are moved with 16-byte vector accesses; shorter ones, short packets
+ *     of a fp32 shard of some 10^4 elements, and the ragged end of a shard
+ *     whose D is not a multiple of 8 are moved element by element.
  *   - Masks are uint8 [N][P] (row i = worker/replica i, column k = packet),
  *     1 = arrived, 0 = lost.
  *   - Return codes: LL_OK (0); LL_EINVAL (-1) for a bad size or argument
@@ -336,8 +337,9 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
                      ll_drift* drift, const ll_ext* ext, void* stream);
 
 /*
- * Pacing of lossy_step_fused and lossy_broadcast (a performance setting of this library, not part
- * of the paper's method; it never changes a result).  The fused step streams
+ * Pacing of lossy_step_fused and lossy_broadcast (a performance setting of this
+ * library, not part of the paper's method; it never changes a result).  The
+ * fused step streams
  * all N gradient rows and all N replica rows of every packet.  When each
  * workgroup walks the rows on its own, the chip has pieces of every row in
  * flight at once and the HBM serves them well below its streaming rate.  A

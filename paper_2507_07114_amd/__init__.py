@@ -244,8 +244,10 @@ def ll_set_pacing(mode: str = "auto", bytes_per_s: float = 6.7e12, gap_us: float
                   lead_us: float = 4.0, overlap: int = 1, resident: int = 1,
                   headroom: float = 1.0, tail_us: float = 3.0, persistent: int = 0,
                   bytes_per_s_f32: float = 6.4e12) -> None:
-    """Process-wide pacing of lossy_step_fused (a performance setting; see
-    include/lossy.h)."""
+    """Process-wide pacing of lossy_step_fused and lossy_broadcast (a
+    performance setting; see include/lossy.h).  The times, overlap and resident
+    are bf16 rows' defaults; while all five are left alone, fp32 rows take
+    their own, and any other value holds for both."""
     if mode not in PACE_MODES:
         raise ValueError(f"unknown pacing mode {mode!r}")
     cfg = Pacing(PACE_MODES[mode], bytes_per_s, gap_us, lead_us, overlap, resident, headroom,

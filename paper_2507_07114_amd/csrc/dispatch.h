@@ -158,8 +158,7 @@ inline bool default_layout(const PaceSetting& st) {
            st.tail_us == kDefaultPaceTailUs;
 }
 
-// Pace of a kernel with a single sweep (the broadcast) whose share of arrived
-// rows the host does not know (see SweepPace).
+// Schedule of a kernel with a single sweep, the broadcast (see SweepPace).
 struct SweepParams {
     int64_t per_round;
     uint64_t fixed;        // of a round besides its slots, 1/256 ticks
@@ -205,25 +204,29 @@ struct PaceTile {
 //              N = 32: 8 M (4) 218 / 230, 13 M (5) 369 / 350, 20 M (8) 578 / 530
 //              N = 24: 16 M (7) 351 / 362, 33 M (13) 721 / 715
 //              N = 16: 16 M 270 / 287, 100 M 1515 / 1646
-//   stale fill, bf16 rows
+//   stale fill, bf16 rows with drift (rounds of 1280 tiles)
 //              N = 64: 8 M (4) 617 / 577, 26 M 1856 / 1783
-//              with drift (rounds in the table are of 1280 tiles), three rounds:
-//              N = 32: 5.3 M 211 / 226, 6 M 237 / 245, 7 M 274 / 276, 7.4 M 301 / 290
-//              N = 40: 5.3 M 259 / 268, 5.9 M 286 / 289, 7 M 339 / 330
-//              N = 48: 5.3 M 308 / 311, 5.6 M 324 / 322, 7 M 401 / 381
-//              four: N = 32 7.9 M 318 / 320, 8.4 M 358 / 332, 20 M (8) 826 / 751
-//              without (of 1536), three: N = 32 7 M 259 / 263, 7.4 M 280 / 276, 8 M
-//              306 / 291;  N = 36: 6.3 M 263 / 269, 7 M 289 / 289, 7.9 M 336 / 319;
-//              N = 48: 7 M 380 / 367;  N = 16: 33 M with drift 684 / 767
+//              N = 48: 5.3 M (3) 308 / 311, 5.6 M (3) 324 / 322, 7 M (3) 401 / 381
+//              N = 40: 5.3 M (3) 259 / 268, 5.9 M (3) 286 / 289, 7 M (3) 339 / 330
+//              N = 32: 5.3 M (3) 211 / 226, 6 M (3) 237 / 245, 7 M (3) 274 / 276,
+//                      7.4 M (3) 301 / 290, 7.9 M (4) 318 / 320, 8.4 M (4) 358 / 332
+//              N = 16: 33 M 684 / 767
+//   the same without drift (of 1536)
+//              N = 48: 7 M (3) 380 / 367
+//              N = 36: 6.3 M (3) 263 / 269, 7 M (3) 289 / 289, 7.9 M (3) 336 / 319
+//              N = 32: 7 M (3) 259 / 263, 7.4 M (3) 280 / 276, 8 M (3) 306 / 291
 //   fp32 rows  N = 64: 4 M (4) 382 / 425, 8 M (8) 802 / 756, 50 M 4725 / 4220
 //              N = 32: 8 M (8) 412 / 413, 16 M (16) 844 / 769
 //              N = 24: 16 M (16) 598 / 605, 25 M (24) 1035 / 908
 //              N = 16: 16 M 425 / 440, 33 M (32) 932 / 856
-//              N = 12: 33 M 727 / 694;  N = 8: 33 M 530 / 531, 100 M 1485 / 1538
+//              N = 14: 26 M (25) 648 / 619, 60 M 1503 / 1376
+//              N = 12: 25.5 M (25) 565 / 546, 33 M 723 / 694, 50 M 1120 / 1030, 80 M
+//                      1765 / 1625;  N = 10: 70 M 1335 / 1257
+//              N = 8: 33 M 530 / 531, 60 M 962 / 937, 100 M 1485 / 1538
 //   stale fill, fp32 rows  N = 32: 16 M 1129 / 1144
-// Three rounds of stale fill gain from 115000 row tiles on, by rows and tiles
-// alike; on flat tiles (without drift) from three rounds (L = 750: N = 32 5.3 M 213
-// / 210, 7.4 M 295 / 285, but 6.3 M 246 / 257; N = 40 5.3 M 265 / 250).
+// Three rounds of stale fill gain from 115000 row tiles (rows x tiles) on; on
+// flat tiles, without drift, for the most part from the start (L = 750: N = 32 5.3
+// M 213 / 210, 6.3 M 246 / 257, 7.4 M 295 / 285; N = 40 5.3 M 265 / 250).
 // Flat tiles with drift gain nothing at any size: their stale rows are read
 // vector by vector, so that the last sweep is no stream (bf16 rows, L = 750: N =
 // 32 10 M 319 / 334, 80 M 2357 / 2369; N = 48 6.4 M 273 / 307; N = 64 5 M 284 /

@@ -304,8 +304,9 @@ __device__ __forceinline__ Chunk<SPLIT> chunk_at(int64_t b, int64_t d, int64_t L
 //              instructions) holding the chunk's valid bytes: its base is the
 //              same for every lane, each lane adds a 32-bit offset, and lanes
 //              past the data read zeros and write nothing, without a branch.
-//   W = false  element by element (a shard end that is not a multiple of 8,
-//              or packets whose length is not a multiple of 8 elements).
+//   W = false  element by element (the shard's end if it is not a multiple of
+//              8, and chunks of packets that do not start on one: lengths below
+//              64, and short packets of few fp32 tiles; see tile_grid).
 // Loads land in raw registers and are unpacked only when used, so several row
 // loads can be in flight together.
 // ---------------------------------------------------------------------------
@@ -604,9 +605,10 @@ struct ClockPace {
     __device__ __forceinline__ void stale(int i) const { at(off_s, ds, i); }
 };
 
-// Pace of a kernel with a single sweep (the broadcast) whose share of arrived rows the host
-// does not know: the anchor kernel samples it from the masks and stores it
-// beside the start time, in 1/65536, and the slots and rounds scale with it.
+// Pace of a kernel with a single sweep (the broadcast) whose share of arrived
+// rows the host does not know: the anchor kernel samples it from the masks and
+// stores it beside the start time, in 1/65536, and the slots and rounds scale
+// with it.
 struct SweepAnchor {
     uint64_t start, arrived;
 };
