@@ -81,6 +81,36 @@ inline TileGrid tile_grid(bool f32_rows, int n, int64_t d, int64_t P, int64_t L,
     return TileGrid{(d + T - 1) / T, 0, slots, flat_lds_bytes(ndir, slots, n)};
 }
 
+// Whether an unpaced call that touches `bytes` in all, on `tiles` tiles, loads
+// its rows with the plain cache policy instead of past the caches.  Up to half
+// of the 256 MiB memory-side cache a program's rows may still be there, from the
+// call or the kernel that wrote them, and plain loads find them sooner.  Streamed
+// / plain, us, one set of buffers again and again; three in turn (p = 0.1):
+//   steps   bf16 N = 6, 3.1 M (84 MiB) 22.1 / 16.8; 22.2 / 16.9
+//           N = 8, 2.5 M (106) 28.0 / 23.7; 30.1 / 23.6   N = 5, 3.3 M (87) 40.2 /
+//           40.2; 41.8 / 39.5   fp32 N = 6, 1.6 M (77) 23.6 / 20.3; 24.5 / 20.4
+//           flat, N = 3, 5.7 M (109) 33.8 / 30.1; 33.9 / 30.6
+//   larger  bf16 N = 3, 8.2 M (157) 70.4 / 66.2; 70.6 / 73.3   N = 12, 2.8 M (163)
+//           54.9 / 54.6; 55.9 / 63.8   N = 4, 7.2 M (164) 43.3 / 41.3; 43.5 / 46.0
+//   alone   drift bf16 N = 4, 3.9 M (45) 18.8 / 18.6; 19.3 / 18.3, N = 61, 0.2 M (24,
+//           396 tiles) 28.7 / 25.6; 34.8 / 31.3, N = 3, 14 M (135) 43.5 / 40.8; 43.6
+//           / 45.9   aggregate bf16 N = 4, 6.7 M (77) 24.1 / 22.9; 24.0 / 22.7
+// With few tiles, each of many rows, streamed loads come back sooner whatever
+// the size: steps N = 71, 0.3 M (159 tiles) 83.9 / 97.4, N = 47, 0.1 M fp32 (98) 25.7
+// / 28.7; 25.7 / 32.8, N = 28, 0.5 M fp32 (512) 61.0 / 66.6; aggregate N = 77, 0.4 M
+// (193) 74.8 / 87.9; drift N = 81, 0.4 M (217) 73.8 / 87.9.  Stale fill, which
+// writes the rows that it reads, gains from fewer tiles and up to more bytes: bf16
+// N = 9, 1.5 M (80, 709 tiles) 20.2 / 17.2; 20.6 / 17.9, N = 13, 2.3 M (187) 61.2 /
+// 58.3; 63.1 / 58.3, 2.8 M (238) 62.3 / 48.3; 63.4 / 56.2, fp32 N = 55, 0.15 M (96,
+// 586) 36.2 / 31.9; 37.2 / 32.3, but bf16 N = 4, 12.5 M (334) 94.1 / 87.3; 94.2 /
+// 101.8.
+constexpr double kMiB = 1048576.0;
+enum KeepCall { kKeepStep, kKeepFill, kKeepDrift };  // (an aggregate alone is as a step)
+inline bool keep_rows(KeepCall call, int64_t tiles, double bytes) {
+    if (call == kKeepFill) return tiles >= 512 && bytes <= 256.0 * kMiB;
+    return tiles >= (call == kKeepDrift ? 256 : 1024) && bytes <= 128.0 * kMiB;
+}
+
 // ---------------------------------------------------------------------------
 // Pacing
 // ---------------------------------------------------------------------------

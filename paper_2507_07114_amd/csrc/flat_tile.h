@@ -310,14 +310,14 @@ __device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t r, int lo, int h
 // Elements `elems` of a row: in whole tiles (W) every vector that holds one of
 // them, with its other elements as they are in memory; else those elements
 // alone.  What is not loaded reads as 0.
-template <class E, bool W, bool SPLIT>
+template <class E, bool W, bool STREAM, bool SPLIT>
 __device__ __forceinline__ void load_flat(const typename E::T* row, const Chunk<SPLIT>& ch,
                                           uint32_t elems, Raw8<E>& x) {
     if (W) {
         const int es = (int)sizeof(typename E::T);
         const int lo = (SPLIT ? (elems & 0x0Fu) : elems) ? ch.lane * es : kBufferPast;
         const int hi = (SPLIT ? (elems & 0xF0u) : elems) ? ch.hi * es : kBufferPast;
-        load_at<row_policy<E, SPLIT>(), SPLIT>(chunk_rsrc(row, ch), lo, hi, x);
+        load_at<row_policy<E, SPLIT, STREAM>(), SPLIT>(chunk_rsrc(row, ch), lo, hi, x);
     } else {
         uint32_t w[8];
 #pragma unroll
@@ -348,7 +348,7 @@ __device__ __forceinline__ void store_flat(typename E::T* row, const Chunk<SPLIT
 
 // stream_rows over the rows of a FlatWalk: use(raw, elems) with what load_flat
 // gives for the lane's elements of each row.
-template <int D, class E, bool W, bool SPLIT, class Walk, class PaceFn, class UseFn>
+template <int D, class E, bool W, bool STREAM, bool SPLIT, class Walk, class PaceFn, class UseFn>
 __device__ __forceinline__ void stream_flat(const typename E::T* rows, int64_t ld,
                                             const Chunk<SPLIT>& ch, Walk& walk, const PaceFn& pace,
                                             const UseFn& use) {
@@ -362,7 +362,7 @@ __device__ __forceinline__ void stream_flat(const typename E::T* rows, int64_t l
     // past the last row the ring issues loads of no element
     auto issue = [&](int row, uint32_t e, Raw8<E>& x) {
         const int at = __builtin_amdgcn_readfirstlane(row >= 0 ? row : first);
-        load_flat<E, W>(rows + (int64_t)at * ld, ch, e, x);
+        load_flat<E, W, STREAM>(rows + (int64_t)at * ld, ch, e, x);
     };
 #pragma unroll
     for (int u = 0; u < D; ++u) {
@@ -424,6 +424,7 @@ __device__ __forceinline__ void aggregate_flat(const typename E::T* grads, int64
                                                const float (&th)[8], const AggVariant& var,
                                                const Pace& pace, float (&g)[8]) {
     constexpr int Q = Flat<SPLIT>::Q;
+    constexpr bool kStream = kStreamRows<Pace>;
     const Chunk<SPLIT>& ch = f.ch;
     const uint64_t* words = lds.words;
     const float nf = (float)f.n;
@@ -456,8 +457,8 @@ __device__ __forceinline__ void aggregate_flat(const typename E::T* grads, int64
                 for (int q = 0; q < Q; ++q)
                     here[u] |= ((mine[q] >> (row & 31)) & 1u) ? f.own(q) : 0u;
                 pace.grad(row);
-                load_flat<E, W>(grads + (int64_t)row * ld, ch, here[u], x[u]);
-                load_flat<E, W>(prev + (int64_t)row * ld, ch, all & ~here[u], y[u]);
+                load_flat<E, W, kStream>(grads + (int64_t)row * ld, ch, here[u], x[u]);
+                load_flat<E, W, kStream>(prev + (int64_t)row * ld, ch, all & ~here[u], y[u]);
             }
 #pragma unroll
             for (int u = 0; u < B; ++u) {
@@ -482,7 +483,7 @@ __device__ __forceinline__ void aggregate_flat(const typename E::T* grads, int64
     const bool ht = var.kind == kEstHorvitzThompson;
     const int owner = ht ? var.owner : -1;
     FlatWalk<SPLIT, false> walk(f, words, owner, lds.sure);
-    stream_flat<FlatDepth<Pace, W>::grad, E, W>(
+    stream_flat<FlatDepth<Pace, W>::grad, E, W, kStream>(
         grads, ld, ch, walk, [&](int row) { pace.grad(row); },
         [&](Raw8<E>& raw, uint32_t elems) {
             if (W && some_elems(elems)) keep_elems(elems, raw);
@@ -505,7 +506,7 @@ __device__ __forceinline__ void aggregate_flat(const typename E::T* grads, int64
         if (owner >= 0) {
             pace.grad(owner);
             Raw8<E> raw;
-            load_flat<E, W>(grads + (int64_t)owner * ld, ch, lossy, raw);
+            load_flat<E, W, kStream>(grads + (int64_t)owner * ld, ch, lossy, raw);
             unpack(raw, mine);
         }
 #pragma unroll

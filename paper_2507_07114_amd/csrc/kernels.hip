@@ -233,7 +233,7 @@ __device__ __forceinline__ Chunk<E::kSplit> chunk_of(int64_t b, int64_t d, int64
 // ---------------------------------------------------------------------------
 // One-stage entry points
 // ---------------------------------------------------------------------------
-template <class G, bool W, bool SPLIT>
+template <class G, class Pace, bool W, bool SPLIT>
 __device__ __forceinline__ void aggregate_chunk(const AggParams& p, const Chunk<SPLIT>& ch,
                                                 const uint64_t* words, int K) {
     float th[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -245,11 +245,11 @@ __device__ __forceinline__ void aggregate_chunk(const AggParams& p, const Chunk<
     const bool relp = p.var.reliable != nullptr && p.var.reliable[ch.k] != 0;
     float g[8];
     aggregate8<G, W>(reinterpret_cast<const typename G::T*>(p.grads), p.ld, ch, words, p.n, K,
-                     p.lam, th, p.var, relp, NoPace(), g);
+                     p.lam, th, p.var, relp, Pace(), g);
     store_chunk<W>(p.g_hat, ch, g);
 }
 
-template <class G>
+template <class G, class Pace>
 __global__ __launch_bounds__(G::kPacketThreads) void k_aggregate(AggParams p) {
     constexpr int NT = G::kPacketThreads;
     __shared__ uint64_t s_words[1][kMaxWords];
@@ -261,13 +261,13 @@ __global__ __launch_bounds__(G::kPacketThreads) void k_aggregate(AggParams p) {
     const int K = popcount_words(s_words[0], nw);
     if (ch.c == 0 && threadIdx.x == 0 && p.counts) p.counts[ch.k] = K;
     if (ch.nv == 0) return;
-    if (ch.whole) aggregate_chunk<G, true>(p, ch, s_words[0], K);
-    else aggregate_chunk<G, false>(p, ch, s_words[0], K);
+    if (ch.whole) aggregate_chunk<G, Pace, true>(p, ch, s_words[0], K);
+    else aggregate_chunk<G, Pace, false>(p, ch, s_words[0], K);
 }
 
 extern __shared__ uint64_t s_flat[];  // masks and weights of a flat tile (see FlatLds)
 
-template <class G, bool W, bool SPLIT>
+template <class G, class Pace, bool W, bool SPLIT>
 __device__ __forceinline__ void aggregate_flat_chunk(const AggParams& p, const Flat<SPLIT>& f,
                                                      const FlatLds& lds) {
     float th[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -284,11 +284,11 @@ __device__ __forceinline__ void aggregate_flat_chunk(const AggParams& p, const F
     }
     float g[8];
     aggregate_flat<G, W>(reinterpret_cast<const typename G::T*>(p.grads), p.ld, f, lds, p.lam, th,
-                         p.var, NoPace(), g);
+                         p.var, Pace(), g);
     store_chunk<W>(p.g_hat, f.ch, g);
 }
 
-template <class G>
+template <class G, class Pace>
 __global__ __launch_bounds__(G::kPacketThreads) void k_aggregate_flat(AggParams p) {
     constexpr int NT = G::kPacketThreads;
     const auto f = flat_at<NT, G::kSplit>(blockIdx.x, p.d, p.L, p.n, p.slots);
@@ -301,8 +301,8 @@ __global__ __launch_bounds__(G::kPacketThreads) void k_aggregate_flat(AggParams 
     if (p.counts && s < f.slots && f.starts_here(s))
         p.counts[f.ch.k + s] = flat_count(lds.words, f, s);
     if (f.ch.nv == 0) return;
-    if (f.ch.whole) aggregate_flat_chunk<G, true>(p, f, lds);
-    else aggregate_flat_chunk<G, false>(p, f, lds);
+    if (f.ch.whole) aggregate_flat_chunk<G, Pace, true>(p, f, lds);
+    else aggregate_flat_chunk<G, Pace, false>(p, f, lds);
 }
 
 // Owner update alone: a stream of up to four vectors in and three out, bound
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_broadcast_flat(BcastParam
 }
 
 // Drift of one chunk over all rows, read in ascending order.
-template <class R, bool W, bool SPLIT>
+template <class R, bool STREAM, bool W, bool SPLIT>
 __device__ __forceinline__ void drift_chunk(const DriftParams& p, const Chunk<SPLIT>& ch, double& pair,
                                             double& range, double& abs_sum) {
     const typename R::T* reps = reinterpret_cast<const typename R::T*>(p.replicas);
@@ -475,7 +475,7 @@ __device__ __forceinline__ void drift_chunk(const DriftParams& p, const Chunk<SP
         unpack(th_r, th);
         pack(th, ref);
     } else {
-        load_row<R, W>(reps, ch, ref);
+        load_row<R, W, STREAM>(reps, ch, ref);
     }
     float r[8];
     unpack(ref, r);
@@ -486,7 +486,7 @@ __device__ __forceinline__ void drift_chunk(const DriftParams& p, const Chunk<SP
 #pragma unroll
         for (int u = 0; u < kBatchDrift; ++u) {
             const int row = i0 + u < p.n ? i0 + u : i0;
-            load_row<R, W>(reps + (int64_t)row * p.ld, ch, raw[u]);
+            load_row<R, W, STREAM>(reps + (int64_t)row * p.ld, ch, raw[u]);
         }
 #pragma unroll
         for (int u = 0; u < kBatchDrift; ++u) {
@@ -501,7 +501,7 @@ __device__ __forceinline__ void drift_chunk(const DriftParams& p, const Chunk<SP
     abs_sum = acc.abs_sum;
 }
 
-template <class R>
+template <class R, bool STREAM>
 __global__ __launch_bounds__(R::kPacketThreads) void k_drift(DriftParams p) {
     constexpr int NT = R::kPacketThreads;
     __shared__ uint64_t s_words[1][kMaxWords];
@@ -516,8 +516,8 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_drift(DriftParams p) {
     }
     double pair = 0.0, range = 0.0, abs_sum = 0.0;
     if (ch.nv > 0) {
-        if (ch.whole) drift_chunk<R, true>(p, ch, pair, range, abs_sum);
-        else drift_chunk<R, false>(p, ch, pair, range, abs_sum);
+        if (ch.whole) drift_chunk<R, STREAM, true>(p, ch, pair, range, abs_sum);
+        else drift_chunk<R, STREAM, false>(p, ch, pair, range, abs_sum);
     }
     block_reduce_partial<NT>(pair, abs_sum, range, stale, 0, p.partials + blockIdx.x);
     if (blockIdx.x == 0 && threadIdx.x == 0) *reduce_counter(p.groups) = 0u;
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_drift(DriftParams p) {
 
 // The same over flat tiles: every row is read whatever its mask, so only the
 // count of stale packets needs to know where packets start.
-template <class R>
+template <class R, bool STREAM>
 __global__ __launch_bounds__(R::kPacketThreads) void k_drift_flat(DriftParams p) {
     constexpr int NT = R::kPacketThreads;
     __shared__ uint32_t s_stale;
@@ -543,8 +543,8 @@ __global__ __launch_bounds__(R::kPacketThreads) void k_drift_flat(DriftParams p)
     }
     double pair = 0.0, range = 0.0, abs_sum = 0.0;
     if (f.ch.nv > 0) {
-        if (f.ch.whole) drift_chunk<R, true>(p, f.ch, pair, range, abs_sum);
-        else drift_chunk<R, false>(p, f.ch, pair, range, abs_sum);
+        if (f.ch.whole) drift_chunk<R, STREAM, true>(p, f.ch, pair, range, abs_sum);
+        else drift_chunk<R, STREAM, false>(p, f.ch, pair, range, abs_sum);
     }
     __syncthreads();
     block_reduce_partial<NT>(pair, abs_sum, range, s_stale, 0, p.partials + blockIdx.x);
@@ -752,7 +752,7 @@ __device__ __forceinline__ void step_chunk(const FusedParams& p, const Chunk<SPL
     unpack(r, rv);
     acc.init(RC > 0, rv);
     RowWalk stale(s_words[1], p.n, true, -1);
-    stream_rows<RingDepth<Pace>::stale, R, W>(
+    stream_rows<RingDepth<Pace>::stale, R, W, kStreamRows<Pace>>(
         reps, p.ld_r, ch, stale, [&](int row) { pace.stale(row); },
         [&](const Raw8<R>& raw) {
             float x[8];
@@ -863,13 +863,14 @@ __device__ __forceinline__ void step_flat_chunk(const FusedParams& p, const Flat
 #pragma unroll
     for (int j = 0; j < 8; ++j) zero = __fmaf_rn(rv[j], 0.0f, zero);
     if (!W || __any(!(zero == 0.0f))) {
-        stream_flat<1, R, W>(reps, p.ld_r, ch, stale, slot, [&](const Raw8<R>& raw, uint32_t elems) {
-            float x[8];
-            unpack(raw, x);
-            acc.add_some(x, rv, elems);
-        });
+        stream_flat<1, R, W, kStreamRows<Pace>>(
+            reps, p.ld_r, ch, stale, slot, [&](const Raw8<R>& raw, uint32_t elems) {
+                float x[8];
+                unpack(raw, x);
+                acc.add_some(x, rv, elems);
+            });
     } else {
-        stream_flat<FlatDepth<Pace, W>::stale, R, W>(
+        stream_flat<FlatDepth<Pace, W>::stale, R, W, kStreamRows<Pace>>(
             reps, p.ld_r, ch, stale, slot, [&](const Raw8<R>& raw, uint32_t elems) {
                 if (elems == 0) return;
                 float x[8];
@@ -951,16 +952,16 @@ __device__ __forceinline__ void step_flat(const FusedParams& p, int64_t tile, co
     else step_flat_w<G, R, DRIFT, false>(p, f, tile, pace, lds);
 }
 
-template <class G, class R, bool DRIFT>
+template <class G, class R, bool DRIFT, class Pace>
 __global__ __launch_bounds__(R::kPacketThreads) void k_step_flat(FusedParams p) {
-    step_flat<G, R, DRIFT>(p, blockIdx.x, NoPace());
+    step_flat<G, R, DRIFT>(p, blockIdx.x, Pace());
 }
 
 // One tile per workgroup.
-template <class G, class R, bool DRIFT>
+template <class G, class R, bool DRIFT, class Pace>
 __global__ __launch_bounds__(R::kPacketThreads) void k_step_fused(FusedParams p) {
     __shared__ uint64_t s_words[2][kMaxWords];
-    step_tile<G, R, DRIFT>(p, blockIdx.x, NoPace(), s_words);
+    step_tile<G, R, DRIFT>(p, blockIdx.x, Pace(), s_words);
 }
 
 // Anchor of the paced step's schedule: the clock time its first round
@@ -1071,7 +1072,7 @@ __device__ __forceinline__ void lean_tile(const FusedParams& p, int64_t tile, Cl
 #pragma unroll
         for (int j = 0; j < 8; ++j) g[j] = 0.0f;
         RowWalk walk(s_words[0], p.n, false, -1);
-        stream_rows<RingDepth<ClockPace>::grad, G, true>(
+        stream_rows<RingDepth<ClockPace>::grad, G, true, true>(
             reinterpret_cast<const typename G::T*>(p.grads), p.ld_g, ch, walk,
             [&](int row) { pace.grad(row); },
             [&](const Raw8<G>& raw) {
@@ -1108,7 +1109,7 @@ __device__ __forceinline__ void lean_tile(const FusedParams& p, int64_t tile, Cl
             unpack(r, rv);
             acc.init(RC > 0, rv);
             RowWalk stale(s_words[1], p.n, true, -1);
-            stream_rows<RingDepth<ClockPace>::stale, R, true>(
+            stream_rows<RingDepth<ClockPace>::stale, R, true, true>(
                 reps, p.ld_r, ch, stale, [&](int row) { pace.stale(row); },
                 [&](const Raw8<R>& raw) {
                     float x[8];
@@ -1223,9 +1224,16 @@ static void launch_aggregate_t(AggParams p, hipStream_t s) {
     const TileGrid t = tile_grid(sizeof(typename G::T) == 4, p.n, p.d, p.P, p.L, 1, 0);
     p.cpp = t.cpp;
     p.slots = t.slots;
-    if (t.slots)
-        hipLaunchKernelGGL(k_aggregate_flat<G>, dim3((unsigned)t.tiles), dim3(NT), t.lds, s, p);
-    else hipLaunchKernelGGL(k_aggregate<G>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
+    const double rows = (double)p.n * p.d * sizeof(typename G::T);
+    const bool fill = p.var.kind == kEstStaleFill;
+    const bool keep = keep_rows(fill ? kKeepFill : kKeepStep, t.tiles,
+                                (fill ? 2 : 1) * rows + 4.0 * p.d);
+    const dim3 grid((unsigned)t.tiles), block(NT);
+    if (t.slots && keep)
+        hipLaunchKernelGGL((k_aggregate_flat<G, KeptRows>), grid, block, t.lds, s, p);
+    else if (t.slots) hipLaunchKernelGGL((k_aggregate_flat<G, NoPace>), grid, block, t.lds, s, p);
+    else if (keep) hipLaunchKernelGGL((k_aggregate<G, KeptRows>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_aggregate<G, NoPace>), grid, block, 0, s, p);
 }
 
 hipError_t launch_aggregate(int gdtype, const AggParams& p, hipStream_t s) {
@@ -1261,8 +1269,13 @@ static int64_t launch_drift_t(DriftParams p, hipStream_t s) {
     const TileGrid t = tile_grid(sizeof(typename R::T) == 4, p.n, p.d, p.P, p.L, 0, kFewStepRows);
     p.cpp = t.cpp;
     p.slots = t.slots;
-    if (t.slots) hipLaunchKernelGGL(k_drift_flat<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
-    else hipLaunchKernelGGL(k_drift<R>, dim3((unsigned)t.tiles), dim3(NT), 0, s, p);
+    const bool keep = keep_rows(kKeepDrift, t.tiles,
+                                (double)p.n * p.d * sizeof(typename R::T) + 4.0 * p.d);
+    const dim3 grid((unsigned)t.tiles), block(NT);
+    if (t.slots && keep) hipLaunchKernelGGL((k_drift_flat<R, false>), grid, block, 0, s, p);
+    else if (t.slots) hipLaunchKernelGGL((k_drift_flat<R, true>), grid, block, 0, s, p);
+    else if (keep) hipLaunchKernelGGL((k_drift<R, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_drift<R, true>), grid, block, 0, s, p);
     return t.tiles;
 }
 
@@ -1479,12 +1492,22 @@ static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStre
         else
             hipLaunchKernelGGL((k_step_paced<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), 0, s,
                                pm, q);
-    } else if (t.slots) {
-        hipLaunchKernelGGL((k_step_flat<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), t.lds, s,
-                           pp);
-    } else {
-        hipLaunchKernelGGL((k_step_fused<G, R, DRIFT>), dim3((unsigned)tiles), dim3(NT), 0, s, pp);
+        return tiles;
     }
+    const double grads = (double)pp.n * pp.d * sizeof(typename G::T);
+    const bool fill = pp.var.kind == kEstStaleFill;
+    const bool keep =
+        keep_rows(fill ? kKeepFill : kKeepStep, tiles,
+                  (fill ? 2 : 1) * grads + (double)pp.n * pp.d * sizeof(typename R::T) +
+                      4.0 * pp.d * (pp.opt.kind + 1));
+    const dim3 blocks((unsigned)tiles), block(NT);
+    if (t.slots && keep)
+        hipLaunchKernelGGL((k_step_flat<G, R, DRIFT, KeptRows>), blocks, block, t.lds, s, pp);
+    else if (t.slots)
+        hipLaunchKernelGGL((k_step_flat<G, R, DRIFT, NoPace>), blocks, block, t.lds, s, pp);
+    else if (keep)
+        hipLaunchKernelGGL((k_step_fused<G, R, DRIFT, KeptRows>), blocks, block, 0, s, pp);
+    else hipLaunchKernelGGL((k_step_fused<G, R, DRIFT, NoPace>), blocks, block, 0, s, pp);
     return tiles;
 }
 

@@ -315,12 +315,13 @@ constexpr int kBufferWord3 = 0x00020000;  // gfx9-family word 3: 32-bit data for
 constexpr int kBufferNonTemporal = 2;
 
 // Cache policy of rows of type E.  A row element is read or written once per
-// step, so rows stream past the caches: 64 long rows read at 6.8 TB/s
+// step, so rows stream past the caches (STREAM): 64 long rows read at 6.8 TB/s
 // non-temporally, 6.0 without.  fp32 rows in the geometry of bf16 ones touch
-// half lines and keep the plain policy (see Chunk).
-template <class E, bool SPLIT>
+// half lines and keep the plain policy (see Chunk), and so do the loads of a
+// small call, whose rows the memory-side cache may hold (see keep_rows).
+template <class E, bool SPLIT, bool STREAM = true>
 constexpr int row_policy() {
-    return sizeof(typename E::T) == 2 || SPLIT ? kBufferNonTemporal : 0;
+    return STREAM && (sizeof(typename E::T) == 2 || SPLIT) ? kBufferNonTemporal : 0;
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int bytes) {
@@ -428,10 +429,10 @@ __device__ __forceinline__ void store_chunk(float* base, const Chunk<SPLIT>& ch,
 }
 
 // Rows of type E (gradients, replicas, last arrived contributions).
-template <class E, bool W, bool SPLIT>
+template <class E, bool W, bool STREAM, bool SPLIT>
 __device__ __forceinline__ void load_row(const typename E::T* row, const Chunk<SPLIT>& ch,
                                          Raw8<E>& r) {
-    if (W) load_buf<row_policy<E, SPLIT>()>(chunk_rsrc(row, ch), ch, r);
+    if (W) load_buf<row_policy<E, SPLIT, STREAM>()>(chunk_rsrc(row, ch), ch, r);
     else load_elems(row, ch, r);
 }
 
@@ -483,7 +484,7 @@ struct RowWalk {
 // size 0.  Every turn of the ring issues the same D loads and the loop is left
 // only at the end of a turn, so the compiler waits for exactly one row before
 // each use.
-template <int D, class E, bool W, bool SPLIT, class PaceFn, class UseFn>
+template <int D, class E, bool W, bool STREAM, bool SPLIT, class PaceFn, class UseFn>
 __device__ __forceinline__ void stream_rows(const typename E::T* rows, int64_t ld,
                                             const Chunk<SPLIT>& ch, RowWalk& walk,
                                             const PaceFn& pace, const UseFn& use) {
@@ -497,7 +498,7 @@ __device__ __forceinline__ void stream_rows(const typename E::T* rows, int64_t l
     auto issue = [&](int row, Raw8<E>& x) {
         const int at = __builtin_amdgcn_readfirstlane(row >= 0 ? row : first);
         if (W)
-            load_buf<row_policy<E, SPLIT>()>(
+            load_buf<row_policy<E, SPLIT, STREAM>()>(
                 row_rsrc(rows + (int64_t)at * ld + ch.c0, row >= 0 ? bytes : 0), ch, x);
         else load_elems(rows + (int64_t)at * ld, ch, x);
     };
@@ -556,6 +557,14 @@ struct NoPace {
     __device__ __forceinline__ void rep(int) const {}
     __device__ __forceinline__ void stale(int) const {}
 };
+
+// The same for a call whose rows the memory-side cache may hold: row loads take
+// the plain policy (see keep_rows).
+struct KeptRows : NoPace {};
+template <class Pace>
+inline constexpr bool kStreamRows = true;
+template <>
+inline constexpr bool kStreamRows<KeptRows> = false;
 
 // Slot times of one round of a paced kernel, in 1/256 clock ticks: the
 // access of row i in the gradient, replica and stale-read sweeps waits for
@@ -711,7 +720,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
                 arr[u] = (uniform64(gm[row >> 6]) >> (row & 63)) & 1;
                 const typename E::T* src = arr[u] ? grads : prev;
                 pace.grad(row);
-                load_row<E, W>(src + (int64_t)row * ld, ch, raw[u]);
+                load_row<E, W, kStreamRows<Pace>>(src + (int64_t)row * ld, ch, raw[u]);
             }
 #pragma unroll
             for (int u = 0; u < kBatchGrad; ++u) {
@@ -732,7 +741,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
     const bool ht = var.kind == kEstHorvitzThompson;
     const int sure_row = (ht && !reliable_packet) ? var.owner : -1;
     RowWalk walk(gm, n, false, sure_row);
-    stream_rows<RingDepth<Pace>::grad, E, W>(
+    stream_rows<RingDepth<Pace>::grad, E, W, kStreamRows<Pace>>(
         grads, ld, ch, walk, [&](int row) { pace.grad(row); },
         [&](const Raw8<E>& raw) {
             float x[8];
@@ -750,7 +759,7 @@ __device__ __forceinline__ void aggregate8(const typename E::T* grads, int64_t l
             if (sure_row >= 0) {
                 pace.grad(sure_row);
                 Raw8<E> raw;
-                load_row<E, W>(grads + (int64_t)sure_row * ld, ch, raw);
+                load_row<E, W, kStreamRows<Pace>>(grads + (int64_t)sure_row * ld, ch, raw);
                 unpack(raw, own);
             }
 #pragma unroll

@@ -27,6 +27,9 @@ void tiles(int f32, int n, int64_t d, int64_t L, int step, int64_t* out) {
     const TileGrid t = tile_grid(f32, n, d, (d + L - 1) / L, L, 2, step ? kFewStepRows : 0);
     out[0] = t.tiles; out[1] = t.slots;
 }
+int keeps(int fill, int drift, int64_t tiles, double bytes) {
+    return keep_rows(fill ? kKeepFill : drift ? kKeepDrift : kKeepStep, tiles, bytes);
+}
 int step_layout(const double* st, int f32, int lean, int flat, int per_cu, int n, int fill,
                 int drift, int unlike, double grad, double rep, double stale, double in,
                 int64_t tiles, int cus, double hz, double* out) {
@@ -95,6 +98,12 @@ def tiles(f32, n, d, L, step=True):
     out = (ctypes.c_int64 * 2)()
     _lib().tiles(int(f32), n, _i64(d), _i64(L), int(step), out)
     return out[0], out[1]
+
+
+def keeps(tiles, nbytes, fill=False, drift=False):
+    """Whether an unpaced call (drift: a drift pass by itself) of so many tiles
+    and bytes loads its rows with the plain cache policy."""
+    return bool(_lib().keeps(int(fill), int(drift), _i64(tiles), ctypes.c_double(nbytes)))
 
 
 def step_layout(f32, n, tiles, *, per_cu=5, lean=False, flat=False, fill=False, unlike=False,

@@ -44,6 +44,16 @@ def test_tiles(f32, n, d, L, step, flat):
     assert count <= P * -(-L // 1024)
 
 
+def test_rows_kept_by_the_caches():
+    half = 128 << 20  # of the 256 MiB memory-side cache
+    assert rules.keeps(1024, half) and not rules.keeps(1024, half + 1)
+    assert not rules.keeps(1023, 1 << 20)
+    assert rules.keeps(256, half, drift=True) and not rules.keeps(255, half, drift=True)
+    assert not rules.keeps(256, half + 1, drift=True)
+    assert rules.keeps(512, half * 2, fill=True) and not rules.keeps(511, half, fill=True)
+    assert not rules.keeps(512, half * 2 + 1, fill=True)
+
+
 @pytest.mark.parametrize("f32,flat,n,tiles,paced", [
     # two rounds (of 2048 bf16 or 1024 fp32 tiles) from 64 workers on
     (False, False, 64, 2048, False), (False, False, 64, 2049, True),
