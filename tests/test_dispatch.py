@@ -44,6 +44,17 @@ def test_tiles(f32, n, d, L, step, flat):
     assert count <= P * -(-L // 1024)
 
 
+@pytest.mark.parametrize("f32,d,L,flat", [
+    (False, 256 * 2560, 256, False), (False, 256 * 2561, 256, True),
+    (False, 264 * 1024, 264, False), (False, 264 * 1025, 264, True),  # off the lines
+    (False, 750 * 20, 750, True), (True, 256 * 4096, 256, False), (True, 256 * 4097, 256, True),
+])
+def test_tiles_of_stale_fill_without_drift(f32, d, L, flat):
+    count, slots = rules.tiles(f32, 20, d, L, fill_only=True)
+    assert (slots > 0) == flat
+    assert flat or count == -(-d // L)  # one chunk a packet
+
+
 def test_rows_kept_by_the_caches():
     half = 128 << 20  # of the 256 MiB memory-side cache
     assert rules.keeps(1024, half) and not rules.keeps(1024, half + 1)

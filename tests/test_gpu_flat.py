@@ -290,3 +290,26 @@ def test_flat_drift_skips_nonfinite_elements_that_arrived(gdtype, p):
     want = parity.torch_drift(rest, ref, d)
     assert want["mean_abs_to_master"] > 0
     parity.check_drift_close(got, want, f"{gdtype} p={p}")
+
+
+def test_stale_fill_without_drift_equals_the_step_with_it():
+    """On both sides of a rule: the step without drift on chunk tiles, the step
+    with drift on flat ones."""
+    n, L, d = 18, 256, 256 * 1500 - 3
+    print(f"stale fill on both tilings n={n} d={d}", flush=True)
+    assert rules.tiles(False, n, d, L, fill_only=True)[1] == 0 < rules.tiles(False, n, d, L)[1]
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    rows = [torch.randn((n, -(-d // 8) * 8), generator=gen, device=DEV).bfloat16()
+            for _ in range(3)]
+    vecs = [torch.randn(d, generator=gen, device=DEV) for _ in range(2)]
+    loss, opt = ll.bernoulli(0.3, seed=9), ll.sgd_momentum(0.01, 0.9)
+    ws = torch.zeros(ll.ll_workspace_bytes(n, d, L), dtype=torch.uint8, device=DEV)
+    out = []
+    for drift in (None, ll.drift_buffer()):
+        (grads, prev, reps), (theta, m) = [x.clone() for x in rows], [x.clone() for x in vecs]
+        ll.lossy_step_fused(d=d, packet=L, step=2, loss_g=loss, loss_b=loss, grads=grads, opt=opt,
+                            theta=theta, replicas=reps, m=m, workspace=ws, drift=drift,
+                            ext=ll.ext("stale_fill", g_prev=prev))
+        out.append((grads, prev, reps, theta, m))
+    for name, x, y in zip(("grads", "g_prev", "replicas", "theta", "m"), *out):
+        assert _bit_equal(x, y), name
