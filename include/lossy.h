@@ -357,9 +357,10 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  *   mode         LL_PACE_AUTO (default): paced where it was measured to pay,
  *                by the number of workers and of rounds (bf16 rows: from 64
  *                workers and 3 rounds, 48 and 4 or 32 and 5, stale fill 32,
- *                3 and workers x tiles of 115000; fp32 rows: 48 and 8 and, but for stale fill, 32 and
- *                16 or 12 and 24; never with drift where packets do not fill
- *                whole chunks); LL_PACE_ALWAYS; LL_PACE_NEVER.
+ *                3 and workers x tiles of 115000; fp32 rows: 48 and 8 and,
+ *                but for stale fill, 32 and 16 or 12 and 24; never with
+ *                drift where packets do not fill whole chunks);
+ *                LL_PACE_ALWAYS; LL_PACE_NEVER.
  *                A round takes every resident workgroup place (bf16
  *                rows) or half of them, at most 1024 tiles (fp32 rows, 4 MiB
  *                of a row per slot).
@@ -417,9 +418,9 @@ LL_API int lossy_step_fused_noalloc(int32_t n, int64_t d, int64_t packet, uint64
  * from 64 workers and 2 rounds, 24 workers and workers x rounds of 160 (and,
  * below 40 workers of whole packets, 5.3 rounds), or one long enough round of
  * 160 workers; fp32 rows from 16 workers, 8 rounds and workers x rounds of
- * 450), with slots for 1.045 of
- * bytes_per_s (1.0625 of bytes_per_s_f32) and for the share of arrived rows
- * that a small kernel, enqueued before it, samples from the masks.
+ * 450), with slots for 1.045 of bytes_per_s (1.0625 of bytes_per_s_f32) and for
+ * the share of arrived rows that a small kernel, enqueued before it, samples
+ * from the masks.
  * ll_set_pacing returns LL_EINVAL for an unknown mode or a field outside the
  * ranges above (bytes_per_s and bytes_per_s_f32 in (0, 1e15), gap_us,
  * lead_us and tail_us in [0, 1e4], persistent 0 or 1 and only with overlap

@@ -79,7 +79,9 @@ inline TileGrid tile_grid(bool f32_rows, int n, int64_t d, int64_t P, int64_t L,
     const int64_t cpp = (L + T - 1) / T;
     const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
     const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
-    const bool small = L % 8 == 0 ? P * cpp <= (f32_rows ? 4096 : fill_only && L % 64 == 0 ? 2560 : 1024)
+    const bool small = L % 8 == 0 ? P * cpp <= (f32_rows                    ? 4096
+                                                : fill_only && L % 64 == 0 ? 2560
+                                                                           : 1024)
                                   : f32_rows && L <= T / 2 && d <= (L <= T / 8 ? 64 : 36) * T;
     if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small)
         return TileGrid{P * cpp, (int)cpp, 0, 0};

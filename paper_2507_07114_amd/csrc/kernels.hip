@@ -1451,8 +1451,8 @@ template <class G, class R, bool DRIFT>
 static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     FusedParams pp = p;
-    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, pp.n, pp.d, pp.P, pp.L, 2, kFewStepRows,
-                                 !DRIFT && pp.var.kind == kEstStaleFill);
+    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, pp.n, pp.d, pp.P, pp.L, 2,
+                                 kFewStepRows, !DRIFT && pp.var.kind == kEstStaleFill);
     const int64_t tiles = t.tiles;
     pp.cpp = t.cpp;
     pp.slots = t.slots;
