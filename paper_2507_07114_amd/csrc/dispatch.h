@@ -58,32 +58,41 @@ constexpr size_t flat_lds_bytes(int ndir, int slots, int n) {
 // 375, N = 64: 33 K 60 / 72, 49 K 68 / 60) and an aggregate (L = 100: 33 K 24 / 27, 81
 // K 25 / 23) gain on flat tiles, and a drift pass of longer packets (L = 750, 33 K:
 // 41 / 36); bf16 rows do at once (L = 333, 33 K: N = 16 35 / 29, N = 64 80 / 77).
-// Steps of stale fill without drift (fill_only), whose flat tiles take two loads
+// Steps of stale fill without drift (kTileFill), whose flat tiles take two loads
 // a row, stay with up to 2560 chunk tiles of bf16 rows that start on the lines (L =
 // 256: N = 16, 0.5 M 18.0 / 21.7, N = 49, 0.34 M 27.4 / 41.4, N = 80, 0.46 M 112 / 117;
 // L = 512: N = 24, 0.58 M 22.6 / 28.6, N = 94, 0.7 M 158 / 218; L = 1024: N = 24, 1.05 M
 // 51.4 / 56.9, N = 20, 1.2 M 29.1 / 28.9, N = 9, 2.3 M 36.6 / 32.3); with drift they
 // gain as others do (L = 256, N = 33, 0.65 M 59.7 / 47.4).
+// A broadcast (kTileWrite) of few long bf16 rows that start on the lines writes
+// them as well from a quarter of a workgroup: chunks of 512 to 1024 elements
+// stay for 4 to 23 rows of more than 768 MiB in all (2.2 GB, L = 512: N = 2 890 / 693,
+// N = 4 549 / 555, N = 8 440 / 480, N = 16 413 / 457, N = 20 407 / 456, 1.5 GB N = 48 266 /
+// 261; L = 1024: N = 4 516 / 541, N = 12 424 / 458, N = 20 419 / 448, 1.5 GB N = 32 278 /
+// 273; L = 256, 1.5 GB: N = 8 441 / 334; L = 1536: N = 8 448 / 471, N = 20 440 / 445, 1 GB
+// N = 12 205 / 211, N = 20 196 / 190, 0.6 GB N = 12 122 / 124, N = 16 106 / 102).
 constexpr int kFewStepRows = 12;
 // Elements of a tile: 4 KiB of a row.
 constexpr int tile_elems(bool f32_rows) { return f32_rows ? 1024 : 2048; }
+enum TileCall { kTileAny, kTileFill, kTileWrite };
 struct TileGrid {
     int64_t tiles;
     int cpp, slots;
     size_t lds;  // dynamic LDS of a flat tile
 };
 inline TileGrid tile_grid(bool f32_rows, int n, int64_t d, int64_t P, int64_t L, int ndir,
-                          int few, bool fill_only = false) {
+                          int few, TileCall call = kTileAny) {
     const int T = tile_elems(f32_rows);
     const int percent = f32_rows ? 95 : (n >= 48 ? 85 : 80);
     const int64_t cpp = (L + T - 1) / T;
     const bool full = L >= kFlatMaxPacket || 100 * L >= percent * cpp * T;
     const bool lines = L % 64 == 0 || (L % 8 == 0 && n < few);
-    const bool small = L % 8 == 0 ? P * cpp <= (f32_rows                    ? 4096
-                                                : fill_only && L % 64 == 0 ? 2560
-                                                                           : 1024)
+    const int64_t line = f32_rows ? 4096 : (call == kTileFill && L % 64 == 0 ? 2560 : 1024);
+    const bool small = L % 8 == 0 ? P * cpp <= line
                                   : f32_rows && L <= T / 2 && d <= (L <= T / 8 ? 64 : 36) * T;
-    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small)
+    const bool writes = call == kTileWrite && !f32_rows && n >= 4 && n < 24 && L % 64 == 0 &&
+                        L >= 512 && L <= 1024 && 2.0 * n * d > 768.0 * 1048576.0;
+    if (L < kFlatMinPacket || L >= kFlatMaxPacket || (full && lines) || small || writes)
         return TileGrid{P * cpp, (int)cpp, 0, 0};
     const int slots = flat_slots(T, L);
     return TileGrid{(d + T - 1) / T, 0, slots, flat_lds_bytes(ndir, slots, n)};

@@ -1370,7 +1370,8 @@ template <class R>
 static void launch_broadcast_t(BcastParams p, hipStream_t s) {
     constexpr int NT = R::kPacketThreads;
     constexpr double kRow = (double)NT * kElems * sizeof(typename R::T);
-    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, p.n, p.d, p.P, p.L, 1, 0);
+    const TileGrid t = tile_grid(sizeof(typename R::T) == 4, p.n, p.d, p.P, p.L, 1, 0,
+                                 kTileWrite);
     p.cpp = t.cpp;
     p.slots = t.slots;
     const dim3 grid((unsigned)t.tiles), block(NT);
@@ -1452,7 +1453,8 @@ static int64_t launch_fused_grd(const FusedParams& p, const PaceHint& h, hipStre
     constexpr int NT = R::kPacketThreads;
     FusedParams pp = p;
     const TileGrid t = tile_grid(sizeof(typename R::T) == 4, pp.n, pp.d, pp.P, pp.L, 2,
-                                 kFewStepRows, !DRIFT && pp.var.kind == kEstStaleFill);
+                                 kFewStepRows,
+                                 !DRIFT && pp.var.kind == kEstStaleFill ? kTileFill : kTileAny);
     const int64_t tiles = t.tiles;
     pp.cpp = t.cpp;
     pp.slots = t.slots;

@@ -23,9 +23,9 @@ void defaults(double* v) {
     v[6] = kDefaultPaceHeadroom; v[7] = kDefaultPaceTailUs; v[8] = kDefaultPacePersistent;
     v[9] = kDefaultPaceRateF32;
 }
-void tiles(int f32, int n, int64_t d, int64_t L, int step, int fill_only, int64_t* out) {
+void tiles(int f32, int n, int64_t d, int64_t L, int step, int call, int64_t* out) {
     const TileGrid t =
-        tile_grid(f32, n, d, (d + L - 1) / L, L, 2, step ? kFewStepRows : 0, fill_only);
+        tile_grid(f32, n, d, (d + L - 1) / L, L, 2, step ? kFewStepRows : 0, (TileCall)call);
     out[0] = t.tiles; out[1] = t.slots;
 }
 int keeps(int fill, int drift, int64_t tiles, double bytes) {
@@ -93,12 +93,12 @@ def defaults():
     return dict(zip(FIELDS, _setting({})))
 
 
-def tiles(f32, n, d, L, step=True, fill_only=False):
+def tiles(f32, n, d, L, step=True, fill_only=False, write=False):
     """(tiles, packets of a flat tile or 0 for chunk tiles) of a fused step and
-    its drift pass, or (step=False) of an aggregate or broadcast by itself;
-    fill_only: a step of stale fill without drift."""
+    its drift pass, or (step=False) of an aggregate or (write=True, too) a
+    broadcast by itself; fill_only: a step of stale fill without drift."""
     out = (ctypes.c_int64 * 2)()
-    _lib().tiles(int(f32), n, _i64(d), _i64(L), int(step), int(fill_only), out)
+    _lib().tiles(int(f32), n, _i64(d), _i64(L), int(step), 2 if write else int(fill_only), out)
     return out[0], out[1]
 
 

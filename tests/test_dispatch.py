@@ -55,6 +55,20 @@ def test_tiles_of_stale_fill_without_drift(f32, d, L, flat):
     assert flat or count == -(-d // L)  # one chunk a packet
 
 
+@pytest.mark.parametrize("f32,n,d,L,flat", [
+    (False, 23, 25_000_000, 512, False), (False, 24, 25_000_000, 512, True),
+    (False, 12, 100_000_000, 448, True), (False, 12, 100_000_000, 520, True),
+    (False, 12, 100_000_000, 1088, True),
+    (False, 16, 3 << 23, 1024, True), (False, 16, (3 << 23) + 1, 1024, False),
+    (False, 3, 200_000_000, 1024, True), (False, 4, 200_000_000, 1024, False),
+    (True, 12, 100_000_000, 512, True),
+])
+def test_tiles_of_a_broadcast_of_few_long_rows(f32, n, d, L, flat):
+    count, slots = rules.tiles(f32, n, d, L, False, write=True)
+    assert (slots > 0) == flat
+    assert flat or count == -(-d // L)
+
+
 def test_rows_kept_by_the_caches():
     half = 128 << 20  # of the 256 MiB memory-side cache
     assert rules.keeps(1024, half) and not rules.keeps(1024, half + 1)

@@ -279,3 +279,21 @@ def test_shard_step_of_streamed_vectors(kind, vectors, more):
     ll.shard_step(spec, 7, theta, g_hat, m=m, v=v, d=d)
     for name, x, y in zip(("theta", "m", "v"), (theta, m, v), want):
         assert torch.equal(x, y), name
+
+
+def test_broadcast_of_few_long_rows_of_short_packets():
+    """Rows of more than 768 MiB in all, on chunk tiles: arrived packets take the
+    rounded master, the others keep their bits."""
+    n, L, d = 16, 1024, (3 << 23) + 5
+    print(f"long broadcast n={n} d={d} L={L}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    P = -(-d // L)
+    arrived = (torch.rand((n, P), generator=gen, device=DEV) >= 0.3).to(torch.uint8)
+    theta = torch.randn(d, generator=gen, device=DEV)
+    reps = torch.zeros((n, d + 3), dtype=torch.bfloat16, device=DEV).fill_(3.0)
+    ll.lossy_broadcast(theta, reps, arrived, d=d, packet=L)
+    own = theta.bfloat16()
+    for i in range(n):
+        here = arrived[i].bool().repeat_interleave(L)[:d]
+        assert torch.equal(reps[i, :d], torch.where(here, own, torch.full_like(own, 3.0))), i
+    assert bool((reps[:, d:] == 3.0).all())
